@@ -750,6 +750,8 @@ template <typename T>
 bool stream_sweeps_2d(hipStream_t st, const Op2<T>& L, int S, Vec<const cx<T>> Xin,
                       Vec<const cx<T>> Ec, Vec<const cx<T>> B, Vec<cx<T>> Xout, Vec<cx<T>> Bc,
                       bool update, int ns) {
+    // launches too small for marching wavefronts run on LDS tiles (same roundings)
+    if (tile_sweeps_2d<T>(st, L, S, Xin, Ec, B, Xout, Bc, update, ns)) return true;
     const bool pro = Ec.base != nullptr, resid = Bc.base != nullptr;
     const int halo = S + (resid ? 2 : 0);
     int kind = -1;
@@ -785,6 +787,7 @@ template <typename T>
 void stream_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<const cx<T>> U,
                    Vec<const cx<T>> R, Vec<cx<T>> Rho, Vec<const cx<T>> B, Vec<cx<T>> X,
                    Vec<cx<T>> Bc, int ns) {
+    if (tile_pre_2d<T>(st, L, Bs, c, U, R, Rho, B, X, Bc, ns)) return;
     const int hss = B.base ? 0 : (U.base ? 1 : 2);
     const int halo = 3 + (hss == 1 ? 1 : 0);
     const bool dir = L.dir != 0u;

@@ -79,6 +79,19 @@ void stream_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<c
                    Vec<const cx<T>> R, Vec<cx<T>> Rho, Vec<const cx<T>> B, Vec<cx<T>> X,
                    Vec<cx<T>> Bc, int ns);
 
+// ---- the same passes on LDS tiles (kernels2d_tile.hip) --------------------
+// Same arguments, roundings and results as the streaming passes, for launches
+// of few nodes: return false (and launch nothing) when the launch is large
+// enough for the streaming kernel, and for sweeps other than (S, prolong,
+// restrict, update) in {(4,1,1,0), (2,1,0,1), (2,1,0,0)}.
+template <typename T>
+bool tile_sweeps_2d(hipStream_t st, const Op2<T>& L, int S, Vec<const cx<T>> Xin, Vec<const cx<T>> Ec,
+                    Vec<const cx<T>> B, Vec<cx<T>> Xout, Vec<cx<T>> Bc, bool update, int ns);
+template <typename T>
+bool tile_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<const cx<T>> U,
+                 Vec<const cx<T>> R, Vec<cx<T>> Rho, Vec<const cx<T>> B, Vec<cx<T>> X, Vec<cx<T>> Bc,
+                 int ns);
+
 // ---- small-level V-cycle in LDS (kernels2d_small.hip) ---------------------
 // Levels 0..nlev-1 of this record are consecutive mesh levels; the last is
 // the coarsest (solved with the dense FP64 inverse).  Offsets are in
