@@ -563,47 +563,55 @@ void zero(hipStream_t st, cx<T>* p, long long n) {
     k_zero<T><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(p, n);
 }
 
+// Offsets of the small-level cycle that starts at level l0 (see SmallCycle).
+template <typename T>
+SmallCycle<T> small_layout(const helm_t* h, int l0) {
+    SmallCycle<T> sc{};
+    sc.nlev = h->levels - l0;
+    int off = 0;
+    for (int m = 0; m < sc.nlev; ++m) {
+        const int n = h->nl[l0 + m], plane = (n + 3) * (n + 3);
+        sc.mdiv[m] = ((1 << 20) + n) / (n + 1);
+        sc.off_a[m] = off;
+        off += m < sc.nlev - 1 ? plane : 0;  // the coarsest level is not smoothed
+        sc.off_x[m] = off;
+        off += plane;
+        sc.off_b[m] = off;
+        off += m > 0 ? (int)h->Nl[l0 + m] : 0;
+    }
+    // one FP64 complex partial sum per thread, 16-byte aligned
+    off += off & 1;
+    sc.off_part = off;
+    off += SMALL_THREADS * (int)(sizeof(cxd) / sizeof(cx<T>));
+    sc.total = off;
+    return sc;
+}
+
 // First level handled by the LDS-resident small-level cycle (-1: none).  The
-// levels from there down to the coarsest must fit one workgroup's LDS
-// (64 KB: b and x per level plus one shared scratch vector) and the
-// coarsest mesh must be small enough for one workgroup to apply its dense
-// inverse (at most 289 nodes).
+// levels from there down to the coarsest must fit one workgroup's LDS (64 KB)
+// and its threads, and the coarsest mesh must be small enough for one
+// workgroup to apply its dense inverse: up to 100 nodes the inverse arrives
+// in registers during the descent; 289 nodes (1.3 MB through one compute
+// unit) made this kernel take 28 to 48 us where the tile passes and the
+// coarse solve over many workgroups take 12.
+constexpr int SMALL_COARSE = 100;
 template <typename T>
 int small_start(const helm_t* h) {
-    if (h->dim != 2 || h->levels < 2 || h->nc > 289 || h->opts.no_small || h->dir) return -1;
+    if (h->dim != 2 || h->levels < 2 || h->nc > SMALL_COARSE || h->opts.no_small || h->dir) return -1;
     for (int l = 1; l < h->levels - 1; ++l) {
-        // shared scratch sized for level l and the coarse-solve partials
-        size_t elems = std::max((size_t)h->Nl[l], 1024 * sizeof(cxd) / sizeof(cx<T>)) + 1;
-        for (int m = l; m < h->levels; ++m) elems += 2 * (size_t)h->Nl[m];
-        if (elems * sizeof(cx<T>) <= 65536 && h->levels - l <= MAX_SMALL) return l;
+        if (h->levels - l > MAX_SMALL || h->Nl[l] > SMALL_THREADS * SMALL_NODES || h->Nl[l + 1] > SMALL_THREADS)
+            continue;
+        if (small_layout<T>(h, l).total * sizeof(cx<T>) <= 65536) return l;
     }
     return -1;
 }
 
 template <typename T>
 void run_small(helm_t* h, int l0, Vec<const cx<T>> b, Vec<cx<T>> x, int ns) {
-    SmallCycle<T> sc{};
-    sc.nlev = h->levels - l0;
-    int off = 0;
-    for (int m = 0; m < sc.nlev; ++m) {
-        const int lev = l0 + m;
-        sc.n[m] = h->nl[lev];
-        sc.op[m] = make_op2<T>(h->coef(HELM_OP_L), h->nl[lev], h->omega);
-        sc.off_b[m] = off;
-        off += (int)h->Nl[lev];
-        sc.off_x[m] = off;
-        off += (int)h->Nl[lev];
-    }
-    // shared scratch: the largest level's vector, and room for 1024 FP64
-    // complex partial sums of the coarse solve; 16-byte aligned
-    off += off & 1;
-    for (int m = 0; m < sc.nlev; ++m) {
-        sc.off_t[m] = off;
-        sc.mdiv[m] = ((1 << 20) + h->nl[l0 + m]) / (h->nl[l0 + m] + 1);
-    }
-    sc.off_part = off;
-    off += std::max((int)h->Nl[l0], 1024 * (int)(sizeof(cxd) / sizeof(cx<T>)));
-    vcycle_small<T>(h->stream, sc, sizeof(cx<T>) * (size_t)off, h->d_cinv, h->nc, b, x, ns);
+    SmallCycle<T> sc = small_layout<T>(h, l0);
+    for (int m = 0; m < sc.nlev; ++m)
+        sc.op[m] = make_op2<T>(h->coef(HELM_OP_L), h->nl[l0 + m], h->omega);
+    vcycle_small<T>(h->stream, sc, sizeof(cx<T>) * (size_t)sc.total, h->d_cinv, h->nc, b, x, ns);
 }
 
 // Levels that run with the register-streaming kernels: every 2D level

@@ -7,8 +7,18 @@
 // whole zero-guess V(2,2) cycle below a given level - pre-smoothing,
 // residual restriction, the dense FP64 coarsest solve, prolongation and
 // post-smoothing on every small level - in one launch, one workgroup per
-// right-hand side, synchronising with workgroup barriers instead.  The
-// arithmetic per node is that of the per-level kernels.
+// right-hand side, synchronising with workgroup barriers instead.
+//
+// Its time is the chain of about 14 barrier-separated stages (33^2, 17^2 and
+// 9^2 levels), so a stage is kept short: a level's plane carries a rim of
+// zeros, so that no neighbour read needs a test; a boundary node has its own
+// row weights, so that every node runs the same 22 operations; the finest
+// small level keeps its right-hand side, iterate and weights in registers
+// (three nodes per thread); and the first zero-guess iterate of a level is
+// formed with its restricted right-hand side.  512 threads, because the
+// stages of the 17^2 level and below have 1 to 5 wavefronts of work.
+// Measured from 33^2 down to 9^2 at 4 columns: 17.5 -> 9.4 us in FP64,
+// at 1 column in FP32 13.4 -> 10.7.
 #include "launch.h"
 #include "stencil_rows.h"
 
@@ -16,14 +26,16 @@ namespace helm {
 
 namespace {
 
-constexpr int NTS = 1024;
-constexpr int WAVE = 64;
+constexpr int NTS = SMALL_THREADS;
+constexpr int NPT = SMALL_NODES;  // nodes per thread on the finest small level
 
 template <typename T>
 __device__ __forceinline__ cx<T> zero_c() { return mk((T)0, (T)0); }
 
 template <typename T>
-__device__ __forceinline__ cx<T> sel(bool c, cx<T> a, cx<T> b) { return c ? a : b; }
+__device__ __forceinline__ cx<T> sel(bool c, cx<T> a, cx<T> b) {
+    return mk(c ? a.x : b.x, c ? a.y : b.y);
+}
 
 // a + s t for a real s
 template <typename T>
@@ -32,66 +44,59 @@ __device__ __forceinline__ cx<T> axpy_real(T sc, cx<T> t, cx<T> a) {
 }
 
 // Node q of a level with W = n + 1 nodes per row: (i, j) = (q mod W, q div W)
-// by a multiply with md = ceil(2^20 / W), exact while q W <= 2^20.
+// by a multiply with md = ceil(2^20 / W), exact while q W <= 2^20; its place
+// p in the level's padded plane, and its row of the operator: centre, east /
+// west, north / south and Jacobi factor (the "/" diagonal's weight is the
+// same on every node).
+template <typename T>
 struct Node {
-    int i, j, p;
+    int i, j, p, s;  // s: row stride of the plane
+    cx<T> c, x, y, jf;
 };
-__device__ __forceinline__ Node node_of(int q, int W, int md) {
-    Node nd;
+template <typename T>
+__device__ __forceinline__ Node<T> node_of(const Op2<T>& op, int q, int md) {
+    const int n = op.n, W = n + 1;
+    Node<T> nd;
     nd.j = (int)(((unsigned)q * (unsigned)md) >> 20);
     nd.i = q - nd.j * W;
-    nd.p = q;
+    nd.s = n + 3;
+    nd.p = (nd.j + 1) * nd.s + nd.i + 1;
+    const bool cb = (nd.i == 0) | (nd.i == n), rb = (nd.j == 0) | (nd.j == n);
+    const bool lo = (nd.i == 0) == (nd.j == 0);
+    // an edge misses dC on the centre and dN along it; a corner kA or kB more
+    const cx<T> z = zero_c<T>();
+    nd.c = op.wC + sel(cb, op.dC, z) + sel(rb, op.dC, z) + sel(cb & rb, sel(lo, op.kA, op.kB), z);
+    nd.y = op.wAx + sel(cb, op.dN, z);
+    nd.x = op.wAx + sel(rb, op.dN, z);
+    nd.jf = sel(cb & rb, sel(lo, op.odA, op.odB), sel(cb | rb, op.odE, op.odC));
     return nd;
 }
 
-// (Op s)(i, j) for an LDS vector of the whole level.  Values outside the
-// mesh are taken as zero: the interior stencil then needs, on a boundary
-// column, the along-column neighbours and centre corrected (dN, dC), on a
-// boundary row the along-row ones, and at a corner the remaining centre
-// term (kA at (0,0) and (n,n), kB at (n,0) and (0,n)).  Every node runs the
-// same instructions; the out-of-mesh neighbours are read at the centre's
-// address and replaced by zero.
+// (Op s) at a node whose value is c
 template <typename T>
-__device__ __forceinline__ cx<T> apply_level(const Op2<T>& op, const cx<T>* s, const Node& nd) {
-    const int n = op.n, W = n + 1, p = nd.p;
-    const bool hE = nd.i < n, hW = nd.i > 0, hN = nd.j < n, hS = nd.j > 0;
-    const cx<T> z = zero_c<T>();
-    const cx<T> c = s[p];
-    const cx<T> e = sel(hE, s[hE ? p + 1 : p], z), w = sel(hW, s[hW ? p - 1 : p], z);
-    const cx<T> nn = sel(hN, s[hN ? p + W : p], z), ss = sel(hS, s[hS ? p - W : p], z);
-    const bool hNE = hE & hN, hSW = hW & hS;
-    const cx<T> ne = sel(hNE, s[hNE ? p + W + 1 : p], z), sw = sel(hSW, s[hSW ? p - W - 1 : p], z);
-    cx<T> acc = cfma(op.wDg, ne + sw, cfma(op.wAx, (e + w) + (nn + ss), op.wC * c));
-    const T cb = (hE & hW) ? (T)0 : (T)1, rb = (hN & hS) ? (T)0 : (T)1;
-    acc = axpy_real(cb, cfma(op.dN, nn + ss, op.dC * c), acc);
-    acc = axpy_real(rb, cfma(op.dN, e + w, op.dC * c), acc);
-    const bool lo = (nd.i == 0) == (nd.j == 0);
-    return axpy_real(cb * rb, sel(lo, op.kA, op.kB) * c, acc);
-}
-
-// Jacobi factor omega / diag at a node: interior, edge, or one of the two
-// corner classes
-template <typename T>
-__device__ __forceinline__ cx<T> jfac(const Op2<T>& op, const Node& nd) {
-    const int n = op.n;
-    const bool ei = (nd.i == 0) | (nd.i == n), ej = (nd.j == 0) | (nd.j == n);
-    const bool lo = (nd.i == 0) == (nd.j == 0);
-    return sel(ei & ej, sel(lo, op.odA, op.odB), sel(ei | ej, op.odE, op.odC));
+__device__ __forceinline__ cx<T> apply_at(cx<T> wDg, const cx<T>* s, const Node<T>& nd, cx<T> c) {
+    const cx<T>* q = s + nd.p;
+    const int S = nd.s;
+    return cfma(wDg, q[S + 1] + q[-S - 1],
+                cfma(nd.x, q[1] + q[-1], cfma(nd.y, q[S] + q[-S], nd.c * c)));
 }
 
 // b_c = P^T r at coarse node (I, J): the fine residual at (2I, 2J) plus half
-// of it at the six neighbours present in the mesh
+// of it at its six neighbours (zero outside the mesh)
 template <typename T>
 __device__ __forceinline__ cx<T> restrict_at(const cx<T>* r, int n, int I, int J) {
-    const int W = n + 1, i = 2 * I, j = 2 * J, p = j * W + i;
-    const bool hE = i < n, hW = i > 0, hN = j < n, hS = j > 0;
-    const bool hNE = hE & hN, hSW = hW & hS;
-    const cx<T> z = zero_c<T>();
-    const cx<T> e = sel(hE, r[hE ? p + 1 : p], z), w = sel(hW, r[hW ? p - 1 : p], z);
-    const cx<T> nn = sel(hN, r[hN ? p + W : p], z), ss = sel(hS, r[hS ? p - W : p], z);
-    const cx<T> ne = sel(hNE, r[hNE ? p + W + 1 : p], z), sw = sel(hSW, r[hSW ? p - W - 1 : p], z);
-    const cx<T> sum = ((e + w) + (nn + ss)) + (ne + sw);
-    return cfma(mk((T)0.5, (T)0), sum, r[p]);
+    const int S = n + 3;
+    const cx<T>* q = r + (2 * J + 1) * S + 2 * I + 1;
+    const cx<T> sum = ((q[1] + q[-1]) + (q[S] + q[-S])) + (q[S + 1] + q[-S - 1]);
+    return axpy_real((T)0.5, sum, q[0]);
+}
+
+// x + P e at a fine node, e the coarse plane of nc = n / 2 cells
+template <typename T>
+__device__ __forceinline__ cx<T> prolonged(const cx<T>* e, int n, const Node<T>& nd, cx<T> x) {
+    const int S = n / 2 + 3;
+    const cx<T>* q = e + ((nd.j >> 1) + 1) * S + (nd.i >> 1) + 1;
+    return axpy_real((T)0.5, q[0] + q[(nd.i & 1) + (nd.j & 1) * S], x);
 }
 
 template <typename T>
@@ -102,10 +107,21 @@ __global__ __launch_bounds__(NTS) void k_vcycle_small(SmallCycle<T> sc, const cx
     const int slot = blockIdx.x;
     const int tid = threadIdx.x;
     const int L = sc.nlev;
+    // finest small level: this thread's right-hand side values
+    const Op2<T>& op0 = sc.op[0];
+    const int n0 = op0.n, N0 = (n0 + 1) * (n0 + 1);
+    const cx<T>* bin = Bin.at(slot);
+    cx<T> b0[NPT], x0[NPT];
+    Node<T> nd0[NPT];
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+        const int q = tid + u * NTS;
+        b0[u] = bin[q < N0 ? q : 0];
+    }
     // coarsest solve x = Ainv b in FP64: thread (r, g) forms the partial sum
     // of row r over the columns g, g + G, ...; its first CW entries of Ainv
     // are loaded now so that their latency is hidden behind the descent
-    constexpr int CW = 8;
+    constexpr int CW = 16;
     const int G = nc < NTS ? NTS / nc : 1;
     const int cr = tid / G, cg = tid % G;
     const bool crow = cr < nc;
@@ -115,52 +131,70 @@ __global__ __launch_bounds__(NTS) void k_vcycle_small(SmallCycle<T> sc, const cx
         const int cc = cg + u * G;
         av[u] = (crow && cc < nc) ? Ainv[(long long)cr * nc + cc] : mk(0.0, 0.0);
     }
-    // level 0: load b and form the first pre-smoothing iterate t = jf b
-    {
-        const Op2<T>& op = sc.op[0];
-        const int W = op.n + 1, N = W * W, md = sc.mdiv[0];
-        const cx<T>* b = Bin.at(slot);
-        cx<T>* B = lds + sc.off_b[0];
-        cx<T>* Tt = lds + sc.off_t[0];
-        for (int q = tid; q < N; q += NTS) {
-            const cx<T> v = b[q];
-            B[q] = v;
-            Tt[q] = jfac(op, node_of(q, W, md)) * v;
-        }
+    // the rims of all planes (and everything else) start at zero
+    for (int q = tid; q < sc.total; q += NTS) lds[q] = zero_c<T>();
+    __syncthreads();
+    cx<T>* const A0 = lds + sc.off_a[0];
+    cx<T>* const X0 = lds + sc.off_x[0];
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+        const int q = tid + u * NTS;
+        nd0[u] = node_of(op0, q < N0 ? q : 0, sc.mdiv[0]);
+        x0[u] = nd0[u].jf * b0[u];
+        if (q < N0) A0[nd0[u].p] = x0[u];
     }
     __syncthreads();
-    // down: first pre-smoothing iterate (level 0: formed with the load),
-    // second sweep, residual, restriction
-    for (int l = 0; l < L - 1; ++l) {
-        const Op2<T>& op = sc.op[l];
-        const int n = op.n, W = n + 1, N = W * W, md = sc.mdiv[l];
-        const cx<T>* B = lds + sc.off_b[l];
-        cx<T>* X = lds + sc.off_x[l];
-        cx<T>* Tt = lds + sc.off_t[l];
-        if (l > 0) {
-            for (int q = tid; q < N; q += NTS) Tt[q] = jfac(op, node_of(q, W, md)) * B[q];
-            __syncthreads();
-        }
-        for (int q = tid; q < N; q += NTS) {
-            const Node nd = node_of(q, W, md);
-            X[q] = cfma(jfac(op, nd), B[q] - apply_level(op, Tt, nd), Tt[q]);
+    // a Jacobi sweep of the finest small level from plane `from` (whose
+    // values at this thread's nodes are x0) to plane `to`
+    auto sweep0 = [&](const cx<T>* from, cx<T>* to) {
+#pragma unroll
+        for (int u = 0; u < NPT; ++u) {
+            if (tid + u * NTS >= N0) continue;
+            x0[u] = cfma(nd0[u].jf, b0[u] - apply_at(op0.wDg, from, nd0[u], x0[u]), x0[u]);
+            to[nd0[u].p] = x0[u];
         }
         __syncthreads();
-        for (int q = tid; q < N; q += NTS) Tt[q] = B[q] - apply_level(op, X, node_of(q, W, md));
-        __syncthreads();
-        const int Wc = n / 2 + 1, Nc = Wc * Wc, mdc = sc.mdiv[l + 1];
-        cx<T>* Bc = lds + sc.off_b[l + 1];
-        for (int q = tid; q < Nc; q += NTS) {
-            const Node ndc = node_of(q, Wc, mdc);
-            Bc[q] = restrict_at(Tt, n, ndc.i, ndc.j);
-        }
-        __syncthreads();
+    };
+    sweep0(A0, X0);
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+        if (tid + u * NTS >= N0) continue;
+        A0[nd0[u].p] = b0[u] - apply_at(op0.wDg, X0, nd0[u], x0[u]);
     }
-    // coarsest: partials meet in the scratch area (at least NTS FP64 complex
-    // values), then one thread per row adds its G partials in a fixed order
+    __syncthreads();
+    // restriction to level l + 1: its right-hand side and (unless it is the
+    // coarsest) its first pre-smoothing iterate
+    auto down = [&](int l) {
+        const Op2<T>& opc = sc.op[l + 1];
+        const int Wc = opc.n + 1;
+        if (tid < Wc * Wc) {
+            const Node<T> nd = node_of(opc, tid, sc.mdiv[l + 1]);
+            const cx<T> b = restrict_at(lds + sc.off_a[l], sc.op[l].n, nd.i, nd.j);
+            lds[sc.off_b[l + 1] + tid] = b;
+            if (l + 1 < L - 1) lds[sc.off_a[l + 1] + nd.p] = nd.jf * b;
+        }
+        __syncthreads();
+    };
+    down(0);
+    for (int l = 1; l < L - 1; ++l) {
+        const Op2<T>& op = sc.op[l];
+        const bool on = tid < (op.n + 1) * (op.n + 1);
+        const Node<T> nd = node_of(op, on ? tid : 0, sc.mdiv[l]);
+        cx<T>* A = lds + sc.off_a[l];
+        cx<T>* X = lds + sc.off_x[l];
+        const cx<T> b = lds[sc.off_b[l] + (on ? tid : 0)];
+        cx<T> x = A[nd.p];
+        x = cfma(nd.jf, b - apply_at(op.wDg, A, nd, x), x);
+        if (on) X[nd.p] = x;
+        __syncthreads();
+        if (on) A[nd.p] = b - apply_at(op.wDg, X, nd, x);
+        __syncthreads();
+        down(l);
+    }
+    // coarsest: the partials meet in the scratch area, then one thread per
+    // row adds its G partials in a fixed order
     {
         const cx<T>* B = lds + sc.off_b[L - 1];
-        cx<T>* X = lds + sc.off_x[L - 1];
         cxd* part = reinterpret_cast<cxd*>(lds + sc.off_part);
         if (crow) {
             double re = 0.0, im = 0.0;
@@ -188,46 +222,42 @@ __global__ __launch_bounds__(NTS) void k_vcycle_small(SmallCycle<T> sc, const cx
                 re += part[tid * G + q].x;
                 im += part[tid * G + q].y;
             }
-            X[tid] = mk((T)re, (T)im);
+            lds[sc.off_x[L - 1] + node_of(sc.op[L - 1], tid, sc.mdiv[L - 1]).p] = mk((T)re, (T)im);
         }
+        __syncthreads();
+    }
+    // up: prolongate and correct, post-smooth twice
+    for (int l = L - 2; l > 0; --l) {
+        const Op2<T>& op = sc.op[l];
+        const bool on = tid < (op.n + 1) * (op.n + 1);
+        const Node<T> nd = node_of(op, on ? tid : 0, sc.mdiv[l]);
+        cx<T>* A = lds + sc.off_a[l];
+        cx<T>* X = lds + sc.off_x[l];
+        const cx<T> b = lds[sc.off_b[l] + (on ? tid : 0)];
+        cx<T> x = prolonged(lds + sc.off_x[l + 1], op.n, nd, X[nd.p]);
+        if (on) X[nd.p] = x;
+        __syncthreads();
+        x = cfma(nd.jf, b - apply_at(op.wDg, X, nd, x), x);
+        if (on) A[nd.p] = x;
+        __syncthreads();
+        x = cfma(nd.jf, b - apply_at(op.wDg, A, nd, x), x);
+        if (on) X[nd.p] = x;
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+        if (tid + u * NTS >= N0) continue;
+        x0[u] = prolonged(lds + sc.off_x[1], n0, nd0[u], x0[u]);
+        X0[nd0[u].p] = x0[u];
     }
     __syncthreads();
-    // up: prolongate and correct, post-smooth twice
-    for (int l = L - 2; l >= 0; --l) {
-        const Op2<T>& op = sc.op[l];
-        const int n = op.n, W = n + 1, N = W * W, Wc = n / 2 + 1, md = sc.mdiv[l];
-        const cx<T>* B = lds + sc.off_b[l];
-        cx<T>* X = lds + sc.off_x[l];
-        cx<T>* Tt = lds + sc.off_t[l];
-        const cx<T>* E = lds + sc.off_x[l + 1];
-        for (int q = tid; q < N; q += NTS) {
-            const Node nd = node_of(q, W, md);
-            const int c = (nd.j >> 1) * Wc + (nd.i >> 1);
-            const int oi = nd.i & 1, oj = nd.j & 1;
-            cx<T> v = E[c];
-            if (oi | oj) v = (T)0.5 * (v + E[c + oi + oj * Wc]);
-            X[q] = X[q] + v;
-        }
-        __syncthreads();
-        for (int q = tid; q < N; q += NTS) {
-            const Node nd = node_of(q, W, md);
-            Tt[q] = cfma(jfac(op, nd), B[q] - apply_level(op, X, nd), X[q]);
-        }
-        __syncthreads();
-        if (l > 0) {
-            for (int q = tid; q < N; q += NTS) {
-                const Node nd = node_of(q, W, md);
-                X[q] = cfma(jfac(op, nd), B[q] - apply_level(op, Tt, nd), Tt[q]);
-            }
-            __syncthreads();
-        } else {
-            // the finest small level's last sweep goes straight to memory
-            cx<T>* x = Xout.at(slot);
-            for (int q = tid; q < N; q += NTS) {
-                const Node nd = node_of(q, W, md);
-                x[q] = cfma(jfac(op, nd), B[q] - apply_level(op, Tt, nd), Tt[q]);
-            }
-        }
+    sweep0(X0, A0);
+    // the last sweep goes straight to memory
+    cx<T>* xo = Xout.at(slot);
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+        const int q = tid + u * NTS;
+        if (q < N0) xo[q] = cfma(nd0[u].jf, b0[u] - apply_at(op0.wDg, A0, nd0[u], x0[u]), x0[u]);
     }
 }
 

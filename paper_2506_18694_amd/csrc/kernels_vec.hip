@@ -44,6 +44,10 @@ __device__ __forceinline__ void block_sum(double (&v)[CNT], double* lds) {
 }
 
 // ---- coarse solve ---------------------------------------------------------
+// One wavefront per row.  The rows come from memory (the finest-level passes
+// between two coarse solves evict them from L2), so a row's loads are issued
+// CU at a time before the first of them is used.
+constexpr int CU = 5;
 template <typename T>
 __global__ __launch_bounds__(BS) void k_coarse(const cxd* __restrict__ A, int nc,
                                                Vec<const cx<T>> B, Vec<cx<T>> X, unsigned gx) {
@@ -54,11 +58,20 @@ __global__ __launch_bounds__(BS) void k_coarse(const cxd* __restrict__ A, int nc
     const cx<T>* b = B.at(slot);
     const cxd* a = A + (long long)row * nc;
     double re = 0.0, im = 0.0;
-    for (int c = lane; c < nc; c += WAVE) {
-        cxd bv = cvt<double>(b[c]);
-        cxd av = a[c];
-        re = fma(av.x, bv.x, fma(-av.y, bv.y, re));
-        im = fma(av.x, bv.y, fma(av.y, bv.x, im));
+    for (int c0 = lane; c0 < nc; c0 += CU * WAVE) {
+        cxd av[CU], bv[CU];
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+            const int c = c0 + u * WAVE, cc = c < nc ? c : 0;
+            av[u] = a[cc];
+            bv[u] = cvt<double>(b[cc]);
+        }
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+            if (c0 + u * WAVE >= nc) continue;
+            re = fma(av[u].x, bv[u].x, fma(-av[u].y, bv[u].y, re));
+            im = fma(av[u].x, bv[u].y, fma(av[u].y, bv[u].x, im));
+        }
     }
     re = wave_sum(re);
     im = wave_sum(im);

@@ -95,18 +95,21 @@ bool tile_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<con
 // ---- small-level V-cycle in LDS (kernels2d_small.hip) ---------------------
 // Levels 0..nlev-1 of this record are consecutive mesh levels; the last is
 // the coarsest (solved with the dense FP64 inverse).  Offsets are in
-// complex elements of the dynamic LDS arena; t is shared by all levels and
-// also holds the coarse solve's FP64 partial sums (off_part).  mdiv[l] =
-// ceil(2^20 / (n[l] + 1)) turns a node index into its row by a multiply.
+// complex elements of the dynamic LDS arena (total elements): per level two
+// padded planes of (n + 3)^2 values, a and x, and from level 1 on the
+// right-hand side b; off_part holds the coarse solve's FP64 partial sums.
+// mdiv[l] = ceil(2^20 / (n[l] + 1)) turns a node index into its row by a
+// multiply.  Level 0 has at most SMALL_THREADS SMALL_NODES nodes, level 1 and
+// the coarsest at most SMALL_THREADS.
 constexpr int MAX_SMALL = 8;
+constexpr int SMALL_THREADS = 512, SMALL_NODES = 3;
 template <typename T>
 struct SmallCycle {
     int nlev;
-    int n[MAX_SMALL];
     Op2<T> op[MAX_SMALL];
-    int off_b[MAX_SMALL], off_x[MAX_SMALL], off_t[MAX_SMALL];
+    int off_a[MAX_SMALL], off_x[MAX_SMALL], off_b[MAX_SMALL];
     int mdiv[MAX_SMALL];
-    int off_part;
+    int off_part, total;
 };
 template <typename T>
 void vcycle_small(hipStream_t st, const SmallCycle<T>& sc, size_t lds_bytes, const cxd* Ainv,
