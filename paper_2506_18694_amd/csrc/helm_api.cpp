@@ -828,10 +828,14 @@ Vec<cx<T>> vcycle3d_zero(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const
     Vec<cx<T>> xc = at_ws<cx<T>>(ws, Lw.mg_x[l + 1], Nc);
     Vec<cx<T>> tc = at_ws<cx<T>>(ws, Lw.mg_t[l + 1], Nc);
     const Vec<const cx<T>> none{};
+    const Vec<cx<T>> nil{};
     const bool two = two_stage3d<T>(true);
-    sweeps3d<T>(h, L, L, F_PRE0, false, 0, (T)1, none, b, none, Vec<cx<T>>{}, t, x, ns, two);
-    rr3d<T>(h->stream, L, cst(x), b, bc, ns);
+    if (!block3d<T>(h->stream, L, L, F_JAC0, 1, false, 0, (T)1, none, b, none, nil, x, bc, ns)) {
+        sweeps3d<T>(h, L, L, F_PRE0, false, 0, (T)1, none, b, none, nil, t, x, ns, two);
+        rr3d<T>(h->stream, L, cst(x), b, bc, ns);
+    }
     Vec<cx<T>> ec = vcycle3d_zero<T>(h, Lw, ws, l + 1, cst(bc), xc, tc, ns);
+    if (block3d<T>(h->stream, L, L, F_JAC, 2, true, 0, (T)1, cst(x), b, cst(ec), nil, t, nil, ns)) return t;
     // the one-stage path ends in x (through t), the two-stage one in t
     Vec<cx<T>> out = two ? t : x;
     sweeps3d<T>(h, L, L, F_JAC, true, 0, (T)1, cst(x), b, cst(ec), Vec<cx<T>>{}, t, out, ns, two);
@@ -862,34 +866,60 @@ void hss_step3d_fused(helm_t* h, const Layout& Lw, void* ws, int ns, int s) {
     const Vec<const cx<T>> none{};
     // the one-stage (FP64) sequence keeps the cycle's iterate in x, with t
     // between its two sweeps; the two-stage (FP32) one alternates x and t
+    const Vec<cx<T>> nil{};
     const bool two = two_stage3d<T>(false), one = !two;
-    if (s == 0) {
+    bool restricted = true;  // b1 formed with the pre-smoothing
+    if (block3d<T>(h->stream, L, Bs, s == 0 ? F_HSS0 : F_HSS, 1, false, 0, c, s == 0 ? none : cst(u), cst(R), none,
+                   rho, x, b1, ns)) {
+        // rho, both zero-guess sweeps and the restriction in one pass
+    } else if (s == 0) {
+        restricted = false;
         sweeps3d<T>(h, L, Bs, F_HSS0, false, 0, c, none, cst(R), none, rho, t, x, ns, two);
-    } else if (one) {
+    } else if (one || h->nl[0] < BLOCK3D_N) {
         // rho = c (R - B u) in one pass, then both zero-guess sweeps on rho
         // in the next (five vectors moved instead of seven)
         STREAMCHK((pass3d<T, T>(h->stream, Bs, Bs, F_RESID, 1, false, 0, c, cst(u), cst(R), none,
-                                Vec<cx<T>>{}, rho, ns)));
-        sweeps3d<T>(h, L, L, F_PRE0, false, 0, (T)1, none, cst(rho), none, Vec<cx<T>>{}, t, x, ns, false);
+                                nil, rho, ns)));
+        restricted = block3d<T>(h->stream, L, L, F_JAC0, 1, false, 0, (T)1, none, cst(rho), none, nil, x, b1, ns);
+        if (!restricted) sweeps3d<T>(h, L, L, F_PRE0, false, 0, (T)1, none, cst(rho), none, nil, t, x, ns, false);
     } else {
+        restricted = false;
         sweeps3d<T>(h, L, Bs, F_HSS, false, 0, c, cst(u), cst(R), none, rho, t, x, ns, two);
     }
     for (int q = 0; q < h->cycles; ++q) {
-        if (q > 0) {
+        if (q > 0 && block3d<T>(h->stream, L, L, F_JAC, 2, false, 0, (T)1, cst(x), cst(rho), none, nil, t, b1, ns)) {
+            std::swap(x, t);
+            restricted = true;
+        } else if (q > 0 && h->nl[0] < BLOCK3D_N) {
+            // the second sweep with the restriction
+            STREAMCHK((pass3d<T, T>(h->stream, L, L, F_JAC, 1, false, 0, (T)1, cst(x), cst(rho), none, nil, t, ns)));
+            STREAMCHK(block3d<T>(h->stream, L, L, F_JAC, 1, false, 0, (T)1, cst(t), cst(rho), none, nil, x, b1, ns));
+            restricted = true;
+        } else if (q > 0) {
+            restricted = false;
             // the pre-smoothing pair from the previous result
             const bool pair = two || HELM_K3_PAIR_PRE_FP64 != 0;
             sweeps3d<T>(h, L, L, F_JAC, false, 0, (T)1, cst(x), cst(rho), none, Vec<cx<T>>{}, t,
                         pair ? t : x, ns, pair);
             if (pair) std::swap(x, t);
         }
-        rr3d<T>(h->stream, L, cst(x), cst(rho), b1, ns);
+        if (!restricted) rr3d<T>(h->stream, L, cst(x), cst(rho), b1, ns);
         Vec<const cx<T>> ec = cst(vcycle3d_zero<T>(h, Lw, ws, 1, cst(b1), x1, t1, ns));
         const bool last = q == h->cycles - 1;
         // the profiled pass: the prolongation with the first (FP64) or both
         // (FP32) post-smoothing sweeps of the cycles before the last; x, rho
         // and e_c (an eighth vector) read, the result written
         const bool prof = h->prof_on && !last && s % helm_s::PROF_EVERY == 0;
-        if (last) {
+        if (h->nl[0] < BLOCK3D_N) {
+            if (prof) h->prof_mark();
+            STREAMCHK(block3d<T>(h->stream, L, L, F_JAC, 2, true, last && s > 0 ? 1 : 0, (T)1, cst(x), cst(rho), ec,
+                                 nil, last ? u : t, nil, ns));
+            if (prof) {
+                h->prof_mark();
+                h->prof_pending_bytes += 3.125 * sizeof(cx<T>) * (double)N * ns;
+            }
+            if (!last) std::swap(x, t);
+        } else if (last) {
             sweeps3d<T>(h, L, L, F_JAC, true, s > 0 ? 1 : 0, (T)1, cst(x), cst(rho), ec, Vec<cx<T>>{},
                         t, u, ns, two);
         } else {

@@ -181,6 +181,20 @@ template <typename T>
 void rr3d(hipStream_t st, const Op3F<T>& L, Vec<const cx<T>> X, Vec<const cx<T>> Bv, Vec<cx<T>> Bc,
           int nslots, int tz = 0);
 
+// ---- the same stages on small 3D levels (kernels3d_block.hip) --------------
+// One pass on whole blocks of the mesh: the first stage, nj Jacobi sweeps, the
+// result to Y (upd = 1: Y += result), and with Bc.base set b_c = P^T (b - L x)
+// of that result on the n/2 mesh.  Supported: F_JAC with nj = 2 and pro, and
+// with the restriction F_JAC0, F_HSS0 (x = w/D b, nj = 1 more sweep), F_JAC
+// with nj = 1 or 2 and F_HSS with nj = 1.  Y must not alias X.  Returns false
+// (and launches nothing) for any other, and for a level large enough for the
+// marching passes.
+constexpr int BLOCK3D_N = 96;  // levels of fewer cells per side
+template <typename T>
+bool block3d(hipStream_t st, const Op3F<T>& L, const Op3F<T>& B, int first, int nj, bool pro, int upd, T s,
+             Vec<const cx<T>> X, Vec<const cx<T>> Bv, Vec<const cx<T>> Ec, Vec<cx<T>> Rho, Vec<cx<T>> Y,
+             Vec<cx<T>> Bc, int ns);
+
 // ---- mixed [DG0]^2 x P1 formulation (kernels2d_mixed.hip) ------------------
 // X, B, Y of mixed vectors [u | sigma] (sigma after the N = (n+1)^2 nodes).
 // y = sb B_u + Op u + G^T (sa sigma + sg g) at the nodes (B, G nullable; G
