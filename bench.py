@@ -58,17 +58,15 @@ def elapsed():
 # counter record depends on.  2D: the finest-level prolongation, four Jacobi
 # sweeps (cycle q's post-smoothing and cycle q+1's pre-smoothing) and the
 # residual restriction in one register-streaming pass.  3D: the
-# finest-level prolongation and the post-smoothing Jacobi sweep(s) of one
-# z-marching pass (one sweep in FP64, two in FP32; the cycles before the
-# last of each HSS step).
+# finest-level prolongation and both post-smoothing Jacobi sweeps of one
+# z-marching pass (the cycles before the last of each HSS step).
 DOMINANT = {
     2: {"tag": "k_stream_sweeps4", "sources": ("kernels2d_stream.hip", "helm_common.h", "stencil_rows.h"),
         "desc": "finest-level prolongation + four Jacobi sweeps + residual restriction "
                 "(k_stream_sweeps<S=4>); x, b, e_c read, x', b_c written"},
     3: {"tag": "k3_pass_prolong", "sources": ("kernels3d_fused.hip", "helm_common.h", "launch.h"),
-        "desc": "finest-level prolongation + Jacobi sweep(s) in one z-marching pass "
-                "(k3_pass<F_JAC, stages, prolong>: one sweep in FP64, two in FP32); "
-                "x, b, e_c read, x' written: 3.125 S N"},
+        "desc": "finest-level prolongation + two Jacobi sweeps in one z-marching pass "
+                "(k3_march<F_JAC, 2 sweeps, prolong>); x, b, e_c read, x' written: 3.125 S N"},
 }
 
 

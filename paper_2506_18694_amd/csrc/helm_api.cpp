@@ -172,28 +172,22 @@ Op3F<T> make_op3f(const Coef& cf, int n, double omega, unsigned dir = 0) {
     for (int q = 0; q < 3; ++q) {
         const zd t1 = uK * pk[q] + uM * pm[q];
         const zd t0 = vK * pk[q] + vM * pm[q];
-        const zd tj = -0.5 * t0 + c * pm[q];
-        o.i1[q] = tocx<T>(t1);
-        o.i0[q] = tocx<T>(t0);
-        o.j0[q] = tocx<T>(tj);  // end plane: T0 / 2 + c PMM
         o.r1[q] = (T)t1.real();
         o.r0[q] = (T)t0.real();
-        o.rj[q] = (T)tj.real();
     }
     // every operator of the primal form has a real stiffness factor a (1, -1
     // or 0), so the imaginary parts are those of the PMM terms:
     // Im(t)[q] = k (h/6)^2 (16, 4, 1)[q]
     o.k1 = (T)(uM.imag() * h6 * h6);
     o.k0 = (T)(vM.imag() * h6 * h6);
-    o.kj = (T)((-0.5 * vM.imag() + c.imag()) * h6 * h6);
+    o.cz = tocx<T>(c * (h6 * h6));  // T0 of an end plane: T0 / 2 + c PMM
     // a column on bx + by boundary lines (bx, by in {0, 1}) halves the centre
     // of the 1D factors in those directions and adds E = 1:
     //   PMM += (-8 h6^2 nb + 4 h6^2 bx by) a0 - 2 h6^2 w
     //   PK  += (-8/6 nb + 4/6 bx by) a0 + w / 6
     //   PG  += (4 h6 nb - 4 h6 bx by) a0 + h6 w
     // with nb = bx + by and w = bx V + by H; so each of T1, T0 changes by
-    // (A nb + C bx by) a0 + B w with (A, B, C) below, and the end-plane
-    // difference (c PMM - T0 / 2) by c times the PMM change minus half of T0's
+    // (A nb + C bx by) a0 + B w with (A, B, C) below
     const double dm[3] = {-8.0 * h6 * h6, -2.0 * h6 * h6, 4.0 * h6 * h6};
     const double dk[3] = {-8.0 / 6.0, 1.0 / 6.0, 4.0 / 6.0};
     const double dg[3] = {4.0 * h6, h6, -4.0 * h6};
@@ -202,7 +196,6 @@ Op3F<T> make_op3f(const Coef& cf, int n, double omega, unsigned dir = 0) {
         const zd d0 = vK * dk[q] + vM * dm[q] + vG * dg[q];
         o.e1[q] = tocx<T>(d1);
         o.e0[q] = tocx<T>(d0);
-        o.f0[q] = tocx<T>(-0.5 * d0 + c * dm[q]);
     }
     // diagonal with nb coordinates on the boundary (factors halved there, E = 1)
     for (int nb = 0; nb < 4; ++nb) {
@@ -458,15 +451,13 @@ void dir_mask(const helm_t* h, hipStream_t st, int l, Vec<cx<T>> Y, int ns) {
 template <typename T, typename TI>
 void op3d(helm_t* h, hipStream_t st, const Coef& cf, int l, int mode, T s, Vec<const cx<TI>> X,
           Vec<const cx<T>> B, Vec<cx<T>> Y, int ns) {
-    if (fused3d(h) && (mode == MODE_APPLY || mode == MODE_RESID || mode == MODE_JACOBI ||
-                       mode == MODE_JACOBI0)) {
-        const Op3F<T> o = make_op3f<T>(cf, h->nl[l], h->omega, h->dir);
-        const int first = mode == MODE_APPLY ? F_APPLY
-                          : mode == MODE_RESID ? F_RESID
-                          : mode == MODE_JACOBI ? F_JAC
-                                                : F_PRE0;
-        STREAMCHK((pass3d<T, TI>(st, o, o, first, 1, false, 0, s, X, B, Vec<const cx<T>>{},
-                                 Vec<cx<T>>{}, Y, ns)));
+    const int first = mode == MODE_APPLY ? F_APPLY : mode == MODE_RESID ? F_RESID : F_JAC;
+    bool fused = fused3d(h) && (mode == MODE_APPLY || mode == MODE_RESID);
+    if constexpr (std::is_same<T, TI>::value) fused = fused || (fused3d(h) && mode == MODE_JACOBI);
+    if (fused) {
+        STREAMCHK((pass3d<T, TI>(st, make_op3f<T>(cf, h->nl[l], h->omega, h->dir), first,
+                                 mode == MODE_JACOBI ? 1 : 0, false, 0, s, X, B, Vec<const cx<T>>{}, Vec<cx<T>>{}, Y,
+                                 Vec<cx<T>>{}, ns)));
         return;
     }
     stencil3d<T, TI>(st, make_op3<T>(cf, h->nl[l], h->omega), mode, s, X, B, Y, ns, !h->opts.no_stream);
@@ -491,7 +482,8 @@ void resid_restrict(helm_t* h, int l, Vec<const cx<T>> X, Vec<const cx<T>> B, Ve
     const Coef cf = h->coef(HELM_OP_L);
     if (fused3d(h)) {
         // Dirichlet faces are cleared inside the pass
-        rr3d<T>(h->stream, make_op3f<T>(cf, h->nl[l], h->omega, h->dir), X, B, Bc, ns);
+        STREAMCHK((pass3d<T, T>(h->stream, make_op3f<T>(cf, h->nl[l], h->omega, h->dir), F_JAC, 0, false, 0, (T)1, X,
+                                B, Vec<const cx<T>>{}, Vec<cx<T>>{}, Vec<cx<T>>{}, Bc, ns)));
     } else if (h->dir) {
         // the residual on the face nodes is not part of the system: cleared
         // before it is restricted, and the coarse face nodes after
@@ -748,72 +740,29 @@ void hss_step_generic(helm_t* h, const Layout& Lw, void* ws, int ns, int s) {
     axpy1<T>(h->stream, N, (T)1, cst(e), u, ns);
 }
 
-// Two Jacobi sweeps on a 3D level through the fused passes, the first of
-// them replaced as `first` says (the zero-guess sweep, the HSS residual with
-// the zero-guess sweep, or a sweep from X, plus P Ec when pro); the second
-// sweep's right-hand side is rho for the HSS forms, else Bv.  upd = 1 adds
-// the result into Y.  In FP32 one pass runs both sweeps as pipeline stages;
-// in FP64 the two-stage pass does not fit the registers of a 1024-thread
-// workgroup, so two one-stage passes run with T in between.
-// prof: bracket the first launch with timing events (the two-stage pass,
-// or the first one-stage pass) and count its algorithmic bytes per column,
-// `bytes` vectors of the level.
-// The fused 3D sweeps in pairs (two stages per pass) in FP32, one per pass
-// in FP64 (whose two-stage kernels exceed the register budget; also on the
-// coarser levels, where halving the launches is worth less than the spills).
-#ifndef HELM_K3_TWO_STAGE_FP32
-#define HELM_K3_TWO_STAGE_FP32 1
-#endif
-#ifndef HELM_K3_TWO_STAGE_COARSE_FP64
-#define HELM_K3_TWO_STAGE_COARSE_FP64 0
-#endif
-#ifndef HELM_K3_TWO_STAGE_FP64
-#define HELM_K3_TWO_STAGE_FP64 0
-#endif
-#ifndef HELM_K3_PAIR_PRE_FP64
-#define HELM_K3_PAIR_PRE_FP64 0
-#endif
+// The zero-guess pre-smoothing x of L x = b on a 3D level and the restriction
+// b_c of its residual, in one pass.
 template <typename T>
-constexpr bool two_stage3d(bool coarse) {
-    return sizeof(T) == 4 ? HELM_K3_TWO_STAGE_FP32 != 0
-                          : (HELM_K3_TWO_STAGE_FP64 != 0 || (coarse && HELM_K3_TWO_STAGE_COARSE_FP64 != 0));
+void pre3d(helm_t* h, const Op3F<T>& L, Vec<const cx<T>> b, Vec<cx<T>> x, Vec<cx<T>> bc, int ns) {
+    const Vec<const cx<T>> none{};
+    const Vec<cx<T>> nil{};
+    if (block3d<T>(h->stream, L, L, F_JAC0, 1, false, 0, (T)1, none, b, none, nil, x, bc, ns)) return;
+    STREAMCHK((pass3d<T, T>(h->stream, L, F_JAC0, 1, false, 0, (T)1, none, b, none, nil, x, bc, ns)));
 }
 
+// Prolongation of ec, correction of x and both post-smoothing sweeps, in one
+// pass; y = the result, or y += it.
 template <typename T>
-void sweeps3d(helm_t* h, const Op3F<T>& L, const Op3F<T>& B, int first, bool pro, int upd, T s,
-              Vec<const cx<T>> X, Vec<const cx<T>> Bv, Vec<const cx<T>> Ec, Vec<cx<T>> Rho,
-              Vec<cx<T>> Tmp, Vec<cx<T>> Y, int ns, bool two, bool prof = false, double bytes = 0.0) {
-    if (prof) h->prof_mark();
-    if (!two && first == F_PRE0 && !pro && upd == 0) {
-        // both zero-guess sweeps in one stencil pass (the first formed on
-        // the staged input planes)
-        STREAMCHK((pass3d<T, T>(h->stream, L, L, F_JAC0, 1, false, 0, (T)1, Vec<const cx<T>>{}, Bv,
-                                Vec<const cx<T>>{}, Vec<cx<T>>{}, Y, ns)));
-        if (prof) {
-            h->prof_mark();
-            h->prof_pending_bytes += sizeof(cx<T>) * (double)ns * bytes;
-        }
-        return;
-    }
-    if (two) {
-        STREAMCHK((pass3d<T, T>(h->stream, L, B, first, 2, pro, upd, s, X, Bv, Ec, Rho, Y, ns)));
-    } else {
-        STREAMCHK((pass3d<T, T>(h->stream, L, B, first, 1, pro, 0, s, X, Bv, Ec, Rho, Tmp, ns)));
-    }
-    if (prof) {
-        h->prof_mark();
-        h->prof_pending_bytes += sizeof(cx<T>) * (double)ns * bytes;
-    }
-    if (two) return;
-    const bool hss = first == F_HSS || first == F_HSS0;
-    STREAMCHK((pass3d<T, T>(h->stream, L, L, F_JAC, 1, false, upd, (T)1, cst(Tmp), hss ? cst(Rho) : Bv,
-                            Vec<const cx<T>>{}, Vec<cx<T>>{}, Y, ns)));
+void post3d(helm_t* h, const Op3F<T>& L, Vec<const cx<T>> x, Vec<const cx<T>> b, Vec<const cx<T>> ec, Vec<cx<T>> y,
+            bool add, int ns) {
+    const Vec<cx<T>> nil{};
+    const int upd = add ? 1 : 0;
+    if (block3d<T>(h->stream, L, L, F_JAC, 2, true, upd, (T)1, x, b, ec, nil, y, nil, ns)) return;
+    STREAMCHK((pass3d<T, T>(h->stream, L, F_JAC, 2, true, upd, (T)1, x, b, ec, nil, y, nil, ns)));
 }
 
-// Fused 3D cycle from a zero initial guess on level l: the two
-// pre-smoothing sweeps (the first from zero), one pass for the residual
-// restriction, the coarser levels, and the prolongation with the two
-// post-smoothing sweeps.  b is read, x and t are this level's work buffers;
+// Fused 3D cycle from a zero initial guess on level l, two passes per level
+// around the coarser ones.  b is read, x and t are this level's work buffers;
 // returns the buffer holding the result (x or t).
 template <typename T>
 Vec<cx<T>> vcycle3d_zero(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const cx<T>> b,
@@ -827,27 +776,22 @@ Vec<cx<T>> vcycle3d_zero(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const
     Vec<cx<T>> bc = at_ws<cx<T>>(ws, Lw.mg_b[l + 1], Nc);
     Vec<cx<T>> xc = at_ws<cx<T>>(ws, Lw.mg_x[l + 1], Nc);
     Vec<cx<T>> tc = at_ws<cx<T>>(ws, Lw.mg_t[l + 1], Nc);
-    const Vec<const cx<T>> none{};
-    const Vec<cx<T>> nil{};
-    const bool two = two_stage3d<T>(true);
-    if (!block3d<T>(h->stream, L, L, F_JAC0, 1, false, 0, (T)1, none, b, none, nil, x, bc, ns)) {
-        sweeps3d<T>(h, L, L, F_PRE0, false, 0, (T)1, none, b, none, nil, t, x, ns, two);
-        rr3d<T>(h->stream, L, cst(x), b, bc, ns);
-    }
+    pre3d<T>(h, L, b, x, bc, ns);
     Vec<cx<T>> ec = vcycle3d_zero<T>(h, Lw, ws, l + 1, cst(bc), xc, tc, ns);
-    if (block3d<T>(h->stream, L, L, F_JAC, 2, true, 0, (T)1, cst(x), b, cst(ec), nil, t, nil, ns)) return t;
-    // the one-stage path ends in x (through t), the two-stage one in t
-    Vec<cx<T>> out = two ? t : x;
-    sweeps3d<T>(h, L, L, F_JAC, true, 0, (T)1, cst(x), b, cst(ec), Vec<cx<T>>{}, t, out, ns, two);
-    return out;
+    post3d<T>(h, L, cst(x), b, cst(ec), t, false, ns);
+    return t;
 }
 
 // One shifted-HSS step s with the fused 3D passes: the residual
-// rho = c (R - B_shift u) together with the first cycle's two pre-smoothing
-// sweeps; per cycle the residual restriction, the coarser levels and the
-// prolongation with two post-smoothing sweeps (cycles after the first start
-// with two sweeps from the previous result); the last sweep adds its result
-// into u (writes it at step 0, u = 0).
+// rho = c (R - B_shift u), then per cycle the two pre-smoothing sweeps (from
+// zero in the first), the residual restriction, the coarser levels and the
+// prolongation with two post-smoothing sweeps; the last sweep adds its result
+// into u (writes it at step 0, u = 0).  On a small level everything before the
+// coarser levels is one pass.  On a large one the residual is a pass of its
+// own, with the zero-guess sweeps and the restriction in the next (rho is read
+// again, but one pass of all three would need three pipeline stages, which do
+// not fit the registers), and a later cycle's sweeps and restriction are two.
+// The cycle's iterate is in x, t its other buffer.
 template <typename T>
 void hss_step3d_fused(helm_t* h, const Layout& Lw, void* ws, int ns, int s) {
     const long long N = h->Nl[0];
@@ -864,69 +808,43 @@ void hss_step3d_fused(helm_t* h, const Layout& Lw, void* ws, int ns, int s) {
     const Op3F<T> L = make_op3f<T>(h->coef(HELM_OP_L), h->nl[0], h->omega, h->dir);
     const Op3F<T> Bs = make_op3f<T>(h->coef(HELM_OP_BSHIFT), h->nl[0], h->omega, h->dir);
     const Vec<const cx<T>> none{};
-    // the one-stage (FP64) sequence keeps the cycle's iterate in x, with t
-    // between its two sweeps; the two-stage (FP32) one alternates x and t
     const Vec<cx<T>> nil{};
-    const bool two = two_stage3d<T>(false), one = !two;
-    bool restricted = true;  // b1 formed with the pre-smoothing
-    if (block3d<T>(h->stream, L, Bs, s == 0 ? F_HSS0 : F_HSS, 1, false, 0, c, s == 0 ? none : cst(u), cst(R), none,
-                   rho, x, b1, ns)) {
-        // rho, both zero-guess sweeps and the restriction in one pass
-    } else if (s == 0) {
-        restricted = false;
-        sweeps3d<T>(h, L, Bs, F_HSS0, false, 0, c, none, cst(R), none, rho, t, x, ns, two);
-    } else if (one || h->nl[0] < BLOCK3D_N) {
-        // rho = c (R - B u) in one pass, then both zero-guess sweeps on rho
-        // in the next (five vectors moved instead of seven)
-        STREAMCHK((pass3d<T, T>(h->stream, Bs, Bs, F_RESID, 1, false, 0, c, cst(u), cst(R), none,
-                                nil, rho, ns)));
-        restricted = block3d<T>(h->stream, L, L, F_JAC0, 1, false, 0, (T)1, none, cst(rho), none, nil, x, b1, ns);
-        if (!restricted) sweeps3d<T>(h, L, L, F_PRE0, false, 0, (T)1, none, cst(rho), none, nil, t, x, ns, false);
-    } else {
-        restricted = false;
-        sweeps3d<T>(h, L, Bs, F_HSS, false, 0, c, cst(u), cst(R), none, rho, t, x, ns, two);
+    hipStream_t st = h->stream;
+    const bool small = h->nl[0] < BLOCK3D_N;
+    if (s == 0) {
+        if (!block3d<T>(st, L, L, F_HSS0, 1, false, 0, c, none, cst(R), none, rho, x, b1, ns))
+            STREAMCHK((pass3d<T, T>(st, L, F_HSS0, 1, false, 0, c, none, cst(R), none, rho, x, b1, ns)));
+    } else if (!block3d<T>(st, L, Bs, F_HSS, 1, false, 0, c, cst(u), cst(R), none, rho, x, b1, ns)) {
+        if (small) STREAMCHK(block3d<T>(st, Bs, Bs, F_RESID, 0, false, 0, c, cst(u), cst(R), none, nil, rho, nil, ns));
+        else STREAMCHK((pass3d<T, T>(st, Bs, F_RESID, 0, false, 0, c, cst(u), cst(R), none, nil, rho, nil, ns)));
+        pre3d<T>(h, L, cst(rho), x, b1, ns);
     }
     for (int q = 0; q < h->cycles; ++q) {
-        if (q > 0 && block3d<T>(h->stream, L, L, F_JAC, 2, false, 0, (T)1, cst(x), cst(rho), none, nil, t, b1, ns)) {
-            std::swap(x, t);
-            restricted = true;
-        } else if (q > 0 && h->nl[0] < BLOCK3D_N) {
-            // the second sweep with the restriction
-            STREAMCHK((pass3d<T, T>(h->stream, L, L, F_JAC, 1, false, 0, (T)1, cst(x), cst(rho), none, nil, t, ns)));
-            STREAMCHK(block3d<T>(h->stream, L, L, F_JAC, 1, false, 0, (T)1, cst(t), cst(rho), none, nil, x, b1, ns));
-            restricted = true;
-        } else if (q > 0) {
-            restricted = false;
-            // the pre-smoothing pair from the previous result
-            const bool pair = two || HELM_K3_PAIR_PRE_FP64 != 0;
-            sweeps3d<T>(h, L, L, F_JAC, false, 0, (T)1, cst(x), cst(rho), none, Vec<cx<T>>{}, t,
-                        pair ? t : x, ns, pair);
-            if (pair) std::swap(x, t);
+        if (q > 0) {
+            if (block3d<T>(st, L, L, F_JAC, 2, false, 0, (T)1, cst(x), cst(rho), none, nil, t, b1, ns)) {
+                std::swap(x, t);
+            } else if (small) {
+                STREAMCHK(block3d<T>(st, L, L, F_JAC, 1, false, 0, (T)1, cst(x), cst(rho), none, nil, t, nil, ns));
+                STREAMCHK(block3d<T>(st, L, L, F_JAC, 1, false, 0, (T)1, cst(t), cst(rho), none, nil, x, b1, ns));
+            } else {
+                STREAMCHK((pass3d<T, T>(st, L, F_JAC, 2, false, 0, (T)1, cst(x), cst(rho), none, nil, t, nil, ns)));
+                std::swap(x, t);
+                STREAMCHK((pass3d<T, T>(st, L, F_JAC, 0, false, 0, (T)1, cst(x), cst(rho), none, nil, nil, b1, ns)));
+            }
         }
-        if (!restricted) rr3d<T>(h->stream, L, cst(x), cst(rho), b1, ns);
         Vec<const cx<T>> ec = cst(vcycle3d_zero<T>(h, Lw, ws, 1, cst(b1), x1, t1, ns));
         const bool last = q == h->cycles - 1;
-        // the profiled pass: the prolongation with the first (FP64) or both
-        // (FP32) post-smoothing sweeps of the cycles before the last; x, rho
-        // and e_c (an eighth vector) read, the result written
+        // the profiled pass: the prolongation with the post-smoothing sweeps
+        // of the cycles before the last; x, rho and e_c (an eighth vector)
+        // read, the result written
         const bool prof = h->prof_on && !last && s % helm_s::PROF_EVERY == 0;
-        if (h->nl[0] < BLOCK3D_N) {
-            if (prof) h->prof_mark();
-            STREAMCHK(block3d<T>(h->stream, L, L, F_JAC, 2, true, last && s > 0 ? 1 : 0, (T)1, cst(x), cst(rho), ec,
-                                 nil, last ? u : t, nil, ns));
-            if (prof) {
-                h->prof_mark();
-                h->prof_pending_bytes += 3.125 * sizeof(cx<T>) * (double)N * ns;
-            }
-            if (!last) std::swap(x, t);
-        } else if (last) {
-            sweeps3d<T>(h, L, L, F_JAC, true, s > 0 ? 1 : 0, (T)1, cst(x), cst(rho), ec, Vec<cx<T>>{},
-                        t, u, ns, two);
-        } else {
-            sweeps3d<T>(h, L, L, F_JAC, true, 0, (T)1, cst(x), cst(rho), ec, Vec<cx<T>>{}, t,
-                        one ? x : t, ns, two, prof, 3.125 * (double)N);
-            if (!one) std::swap(x, t);
+        if (prof) h->prof_mark();
+        post3d<T>(h, L, cst(x), cst(rho), ec, last ? u : t, last && s > 0, ns);
+        if (prof) {
+            h->prof_mark();
+            h->prof_pending_bytes += 3.125 * sizeof(cx<T>) * (double)N * ns;
         }
+        if (!last) std::swap(x, t);
     }
 }
 

@@ -10,8 +10,8 @@
 // side of the region, so the halo is recomputed (a two-sweep pass of TZ planes
 // forms TZ + 2 planes of the first sweep), which costs nothing while most
 // compute units would idle.  Two passes per level and cycle take the place of
-// four (FP64) or three (FP32): the pre-smoothing with the residual
-// restriction, and the prolongation with the post-smoothing.
+// four or more: the pre-smoothing with the residual restriction, and the
+// prolongation with the post-smoothing.
 //
 // Row of node (i, j, l), as in the marching passes: L x = T1(l-1) + T1(l+1) +
 // T0(l), with T1, T0 linear in the four in-plane sums of a plane's
@@ -83,14 +83,15 @@ __device__ __forceinline__ cx<T> col_sum(const ColW<T>& w, cx<T> a0, cx<T> H, cx
 template <int U>
 using IC = std::integral_constant<int, U>;
 
-// FIRST, NJ, PRO, UPD, RR as in pass3d: the first stage, NJ Jacobi sweeps, P
+// FIRST, NJ, PRO, UPD, RR as for pass3d: the first stage, NJ Jacobi sweeps, P
 // e_c added to the input, Y += result, and the restriction of the last x's
 // residual.  TZ: output planes (coarse planes with RR).
 template <typename T, int FIRST, int NJ, bool PRO, bool RR, int LW, int LH, int TZ>
 struct Block {
     static constexpr bool J0 = FIRST == F_JAC0 || FIRST == F_HSS0;  // first sweep formed while staging
     static constexpr bool HSS = FIRST == F_HSS;
-    static constexpr int M = NJ + (HSS ? 1 : 0) + (RR ? 1 : 0);  // stencil stages
+    static constexpr bool ONE = FIRST == F_RESID;
+    static constexpr int M = NJ + (HSS || ONE ? 1 : 0) + (RR ? 1 : 0);  // stencil stages
     static constexpr int NO = RR ? 2 * TZ + 1 : TZ;              // output planes of the last stage
     static constexpr int NP = NO + 2 * M;                        // input planes
     static constexpr int RIM = RR ? M + 1 : M;
@@ -101,7 +102,8 @@ struct Block {
     static constexpr int CW = LW / 2 + 1, CH = LH / 2 + 1, NC = (NP + 1) / 2 + 1;  // coarse values under a region
     // LDS: the input planes (later every second stage's), the first stage's
     // planes, and the coarse planes in the latter's place before that
-    static constexpr int ELEMS = NP * PLANE + ((NP - 2) * PLANE > (PRO ? NC * CW * CH : 0) ? (NP - 2) * PLANE : NC * CW * CH);
+    static constexpr int SECOND = M > 1 || RR ? (NP - 2) * PLANE : 1;
+    static constexpr int ELEMS = NP * PLANE + (PRO && NC * CW * CH > SECOND ? NC * CW * CH : SECOND);
     static_assert(M >= 1 && OWN > 0 && OWNH > 0, "region too small");
 };
 
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(LW * LH) void k3_block(Op3F<T> L, Op3F<T> B, T s, V
     cx<T> v[NP], bv[NP], yo[UPD == 1 ? TZ : 1];
     const cx<T>* xs = C::J0 ? nullptr : X.at(slot);
     const cx<T>* bs = Bv.at(slot);
-    cx<T>* ys = NJ > 0 ? Y.at(slot) : nullptr;
+    cx<T>* ys = NJ > 0 || C::ONE ? Y.at(slot) : nullptr;
     cx<T>* rs = WRHO ? Rho.at(slot) : nullptr;
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
@@ -240,13 +242,22 @@ __global__ __launch_bounds__(LW * LH) void k3_block(Op3F<T> L, Op3F<T> B, T s, V
             const cx<T> a2 = (c[-LW - 1] + c[-LW + 1]) + (c[LW - 1] + c[LW + 1]);
             const cx<T> t1 = col_sum(w1, a0, H, V, a2);
             cx<T> t0 = col_sum(w0, a0, H, V, a2);
-            if (pi == 0 || pi == n) t0 = t0 + col_sum(col_weights<T>(A.rj, A.kj, A.f0, bx, by), a0, H, V, a2);
+            if (pi == 0 || pi == n) {
+                // an end plane: T0 / 2 + cz times this column's mass pattern
+                const T fx = bx ? (T)1 : (T)0, fy = by ? (T)1 : (T)0;
+                const T ma = (T)16 - (T)8 * (fx + fy) + (T)4 * fx * fy, mh = (T)4 - (T)2 * fy, mv = (T)4 - (T)2 * fx;
+                const cx<T> m = mk(fmat(ma, a0.x, fmat(mh, H.x, fmat(mv, V.x, a2.x))),
+                                   fmat(ma, a0.y, fmat(mh, H.y, fmat(mv, V.y, a2.y))));
+                t0 = cfma(A.cz, m, (T)0.5 * t0);
+            }
             if (q >= 2) {
                 const int l = pi - 1;  // output plane
                 const cx<T> r = bv[k + q - 1] - (acc + t1);
                 cx<T> x;
                 if constexpr (RES) {
                     x = csel(inmesh && (unsigned)l <= (unsigned)n, r, z);
+                } else if constexpr (C::ONE) {
+                    x = s * r;
                 } else if constexpr (FHSS) {
                     const cx<T> rho = dfix(s * r, l);
                     bv[k + q - 1] = rho;
@@ -365,6 +376,15 @@ bool block3d(hipStream_t st, const Op3F<T>& L, const Op3F<T>& B, int first, int 
         if (first == F_JAC && nj == 2) HELM_B3(F_JAC, 2, false, 0, true, 16, 16, 1);
         if (first == F_HSS && nj == 1) HELM_B3(F_HSS, 1, false, 0, true, 16, 16, 1);
         return false;
+    }
+    if (!pro && upd == 0 && (first == F_RESID || (first == F_JAC && nj == 1))) {
+        using S = Block<T, F_JAC, 1, false, false, 16, 16, 2>;
+        if (units_of<S>(n, n + 1, 2, ns) <= FEW) {
+            if (first == F_RESID) HELM_B3(F_RESID, 0, false, 0, false, 16, 16, 2);
+            HELM_B3(F_JAC, 1, false, 0, false, 16, 16, 2);
+        }
+        if (first == F_RESID) HELM_B3(F_RESID, 0, false, 0, false, 16, 16, 4);
+        HELM_B3(F_JAC, 1, false, 0, false, 16, 16, 4);
     }
     if (first != F_JAC || nj != 2 || !pro) return false;
     using S = Block<T, F_JAC, 2, true, false, 16, 16, 2>;

@@ -135,61 +135,52 @@ void prolong3d(hipStream_t st, int n, Vec<const cx<T>> E, Vec<cx<T>> X, int nslo
 // c for the end planes, and omega / D by the number of coordinates of the
 // node on the mesh boundary (0 interior, 1 face, 2 edge, 3 corner; the
 // diagonal is symmetric in the three axes).
-// Interior columns (no boundary line in x or y) use T1 = i1[0] a0 +
-// i1[1] (H + V) + i1[2] a2 and T0 = i0[.] likewise, and on the first and
-// last plane T0/2 + c PMM = j0[.] likewise.
 template <typename T>
 struct Op3F {
-    cx<T> i1[3], i0[3], j0[3];  // T1, T0, and T0 of an end plane minus T0, on interior columns
-    // the same weights split (the K factor a is real): real parts, and the
-    // imaginary parts as k * (16, 4, 1) (the in-plane mass pattern)
-    T r1[3], r0[3], rj[3];
-    T k1, k0, kj;
-    cx<T> e1[3], e0[3], f0[3];  // their changes on a boundary column (see kernels3d_fused.hip)
+    // weights of (a0, H + V, a2) on interior columns in T1 and T0, split (the
+    // K factor a is real): real parts, and the imaginary parts as
+    // k * (16, 4, 1) (the in-plane mass pattern m)
+    T r1[3], r0[3];
+    T k1, k0;
+    cx<T> cz;            // T0 of an end plane: T0 / 2 + cz m
+    cx<T> e1[3], e0[3];  // changes on a boundary column (see kernels3d_fused.hip)
     cx<T> od[4];
     int n;
     unsigned dir;  // Dirichlet faces (x0=1 .. z1=32): every pass writes zero on their nodes
 };
 struct Grid3F {
-    int tiles_x, tiles_y, segs, tz;  // tiles per side, plane segments, planes per segment
+    int tiles_x, tiles_y, slots;     // tiles per side, columns
+    int tz, segs, tz_e, segs_e;      // planes per segment and segments: interior and rim tiles
+    unsigned eblocks;                // workgroups of the rim tiles
 };
 // first stage of a fused pass
 enum Pass3First : int {
     F_APPLY = 0,  // y = L x
     F_RESID = 1,  // y = s (b - L x)
-    F_JAC = 2,    // x1 = x + w/D (b - L x)   (x + P e_c with the prolongation)
-    F_HSS = 3,    // rho = s (R - B u), x1 = w/D rho
-    F_HSS0 = 4,   // rho = s R, x1 = w/D rho
-    F_PRE0 = 5,   // x1 = w/D b
-    F_JAC0 = 6,   // x1 = x0 + w/D (b - L x0), x0 = w/D b: both zero-guess sweeps
+    F_JAC = 2,    // nj sweeps x + w/D (b - L x) from x (from x + P e_c with the prolongation)
+    F_HSS = 3,    // rho = s (R - B u), x = w/D rho, then nj sweeps with b = rho
+    F_HSS0 = 4,   // rho = s R, x = w/D rho, then nj sweeps with b = rho
+    F_JAC0 = 5,   // x = w/D b, then nj sweeps
 };
-// One fused pass: the first stage, and with ns = 2 a Jacobi sweep on its
-// output (b = rho for the HSS forms).  Supported: ns = 1 with F_APPLY,
-// F_RESID, F_JAC, F_PRE0 (any TI), and (TI = T) F_JAC with pro (the input
-// is X + P Ec) or upd = 1 (Y += result), F_HSS, F_HSS0, F_JAC0 (X unused:
-// the input planes are w/D b, formed from Bv); ns = 2 (TI = T)
-// with F_JAC (pro, upd as before), F_HSS, F_HSS0, F_PRE0.  X, Bv,
-// Ec, Rho, Y as the form needs; Y must not alias X.  tz: planes per
-// segment (0 = from the launch shape).  Returns false (and launches
-// nothing) for an unsupported combination.
+// One fused pass: the first stage, nj sweeps, the result to Y (upd = 1:
+// Y += result), and with Bc.base set b_c = P^T (b - L x) on the n/2 mesh.
+// Supported: F_APPLY and F_RESID (any TI), and (TI = T) F_JAC with nj = 1 or
+// 2, with nj = 2 and pro (the input is X + P Ec; upd 0 or 1), and with the
+// restriction F_JAC with nj = 0 (Y unused), F_HSS0 and F_JAC0 with nj = 1.  X,
+// Bv, Ec, Rho, Y as the form needs (rho goes to Rho); Y must not alias X.
+// Returns false (and launches nothing) for an unsupported combination.
 template <typename T, typename TI>
-bool pass3d(hipStream_t st, const Op3F<T>& L, const Op3F<T>& B, int first, int ns, bool pro, int upd,
-            T s, Vec<const cx<TI>> X, Vec<const cx<T>> Bv, Vec<const cx<T>> Ec, Vec<cx<T>> Rho,
-            Vec<cx<T>> Y, int nslots, int tz = 0);
-// b_c = P^T (b - L x), the n mesh to the n/2 mesh, in one pass
-template <typename T>
-void rr3d(hipStream_t st, const Op3F<T>& L, Vec<const cx<T>> X, Vec<const cx<T>> Bv, Vec<cx<T>> Bc,
-          int nslots, int tz = 0);
+bool pass3d(hipStream_t st, const Op3F<T>& L, int first, int nj, bool pro, int upd, T s, Vec<const cx<TI>> X,
+            Vec<const cx<T>> Bv, Vec<const cx<T>> Ec, Vec<cx<T>> Rho, Vec<cx<T>> Y, Vec<cx<T>> Bc, int nslots);
 
 // ---- the same stages on small 3D levels (kernels3d_block.hip) --------------
-// One pass on whole blocks of the mesh: the first stage, nj Jacobi sweeps, the
-// result to Y (upd = 1: Y += result), and with Bc.base set b_c = P^T (b - L x)
-// of that result on the n/2 mesh.  Supported: F_JAC with nj = 2 and pro, and
-// with the restriction F_JAC0, F_HSS0 (x = w/D b, nj = 1 more sweep), F_JAC
-// with nj = 1 or 2 and F_HSS with nj = 1.  Y must not alias X.  Returns false
-// (and launches nothing) for any other, and for a level large enough for the
-// marching passes.
-constexpr int BLOCK3D_N = 96;  // levels of fewer cells per side
+// One pass on whole blocks of the mesh; arguments as for pass3d, B the second
+// operator of F_HSS.  Supported: F_RESID, F_JAC with nj = 1, with nj = 2 and
+// pro (upd 0 or 1), and with the restriction F_JAC0 and F_HSS0 with nj = 1,
+// F_JAC with nj = 1 or 2 and F_HSS with nj = 1.  Returns false (and launches
+// nothing) for any other, for a level of BLOCK3D_N cells or more, and where
+// the three stages of the last two would not fit the chip at once.
+constexpr int BLOCK3D_N = 96;  // cells per side from which the marching passes are faster
 template <typename T>
 bool block3d(hipStream_t st, const Op3F<T>& L, const Op3F<T>& B, int first, int nj, bool pro, int upd, T s,
              Vec<const cx<T>> X, Vec<const cx<T>> Bv, Vec<const cx<T>> Ec, Vec<cx<T>> Rho, Vec<cx<T>> Y,
