@@ -367,8 +367,8 @@ struct Layout {
     size_t dh, dh2, dnorm, part, npart, dy, cols, maps, flag;
     // W variant: per level the GMRES smoother's Krylov basis (m+1 vectors
     // per slot), its Hessenberg columns (two passes), norms, coefficients
-    // and reduction partials
-    size_t gk[32], ghu, ghu2, gn, gy, gpart, gnpart;
+    // and reduction partials (two sets)
+    size_t gk[32], ghu, ghu2, gn, gy, gpart, gpart2, gnpart;
     size_t mg;  // mixed: the per-step triangle data g of every slot
     size_t total;
     int cap;    // columns the layout was made for (its offsets depend on it)
@@ -419,8 +419,10 @@ Layout layout(const helm_t* h, int nrhs) {
         L.ghu2 = take(sizeof(cxd) * (size_t)nrhs * (m + 1));
         L.gn = take(sizeof(double) * (size_t)nrhs * (m + 1));
         L.gy = take(sizeof(cxd) * (size_t)nrhs * m);
-        L.gpart = take(sizeof(cxd) * (size_t)nrhs * (m + 1) * nblk);
-        L.gnpart = take(sizeof(double) * (size_t)nrhs * nblk);
+        const int gblk = std::max(nblk, (int)((N + GMRES_BLOCK - 1) / GMRES_BLOCK));
+        L.gpart = take(sizeof(cxd) * (size_t)nrhs * (m + 1) * gblk);
+        L.gpart2 = take(sizeof(cxd) * (size_t)nrhs * (m + 1) * gblk);
+        L.gnpart = take(sizeof(double) * (size_t)nrhs * gblk);
     }
     L.total = off;
     return L;
@@ -492,7 +494,7 @@ void resid_restrict(helm_t* h, int l, Vec<const cx<T>> X, Vec<const cx<T>> B, Ve
         else restrict3d<T>(h->stream, h->nl[l], cst(tmp), Bc, ns);
         dir_mask<T>(h, h->stream, l + 1, Bc, ns);
     } else if (h->dim == 2) {
-        resid_restrict2d<T>(h->stream, make_op2<T>(cf, h->nl[l], h->omega), X, B, Bc, ns);
+        tile_restrict_2d<T>(h->stream, make_op2<T>(cf, h->nl[l], h->omega), X, B, Bc, ns);
     } else {
         stencil3d<T, T>(h->stream, make_op3<T>(cf, h->nl[l], h->omega), MODE_RESID, (T)1, X, B,
                         tmp, ns, !h->opts.no_stream);

@@ -124,7 +124,8 @@ struct TileGrid {
 };
 
 // x <- x_in [+ P e_c]; S Jacobi sweeps; write x, or u += x (UPDATE); with
-// RESID also b_c = P^T (b - L x): k_stream_sweeps on tiles.
+// RESID also b_c = P^T (b - L x): k_stream_sweeps on tiles.  S = 0: only the
+// residual and its restriction.
 template <typename T, int TW, int TH, int S, bool PROLONG, bool RESID, bool UPDATE, bool DIR>
 __global__ __launch_bounds__(TW * TH) void k_tile_sweeps(Op2<T> L, Vec<const cx<T>> Xin,
                                                          Vec<const cx<T>> Ec, Vec<const cx<T>> Bv,
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(TW * TH) void k_tile_sweeps(Op2<T> L, Vec<const cx<
     const Node<T> nd = node_at<T, DIR>(L, (b0 % g.tx) * OW - HALO + x0, (b0 / g.tx) * OH - HALO + y0);
     const bool own = nd.in && x0 >= HALO && x0 < TW - HALO && y0 >= HALO && y0 < TH - HALO;
     const long long np = L.n + 1, npc = L.n / 2 + 1, p = (long long)nd.jc * np + nd.ic;
-    cx<T>* xo = Xout.at(slot);
+    cx<T>* xo = S > 0 ? Xout.at(slot) : nullptr;
     cx<T> v = Xin.at(slot)[p];
     const cx<T> b = Bv.at(slot)[p];
     cx<T> uo = zero_cx<T>();
@@ -157,7 +158,7 @@ __global__ __launch_bounds__(TW * TH) void k_tile_sweeps(Op2<T> L, Vec<const cx<
         v = kept(nd, cfma(nd.jf, b - apply_at<T, TW, TH>(L, pl[(s - 1) & 1], lx, ly, nd, nd.kc, v), v));
         if (s < S || RESID) pl[s & 1][ly][lx] = v;
     }
-    if (own) xo[p] = UPDATE ? uo + v : v;
+    if (S > 0 && own) xo[p] = UPDATE ? uo + v : v;
     if constexpr (RESID) {
         __syncthreads();
         const cx<T> r = kept(nd, b - apply_at<T, TW, TH>(L, pl[S & 1], lx, ly, nd, nd.kc, v));
@@ -271,6 +272,15 @@ bool tile_sweeps_2d(hipStream_t st, const Op2<T>& L, int S, Vec<const cx<T>> Xin
 }
 
 template <typename T>
+void tile_restrict_2d(hipStream_t st, const Op2<T>& L, Vec<const cx<T>> X, Vec<const cx<T>> B, Vec<cx<T>> Bc, int ns) {
+    const TileGrid g = tile_grid(L.n, 2, 16);
+    const unsigned nb = (unsigned)(g.tx * g.ty * ns);
+    const Vec<const cx<T>> none{};
+    const Vec<cx<T>> nil{};
+    k_tile_sweeps<T, TW, 16, 0, false, true, false, false><<<nb, TW * 16, 0, st>>>(L, X, none, B, nil, Bc, g);
+}
+
+template <typename T>
 bool tile_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<const cx<T>> U,
                  Vec<const cx<T>> R, Vec<cx<T>> Rho, Vec<const cx<T>> B, Vec<cx<T>> X, Vec<cx<T>> Bc,
                  int ns) {
@@ -302,6 +312,8 @@ template bool tile_sweeps_2d<double>(hipStream_t, const Op2<double>&, int, Vec<c
                                      Vec<const cxd>, Vec<cxd>, Vec<cxd>, bool, int);
 template bool tile_sweeps_2d<float>(hipStream_t, const Op2<float>&, int, Vec<const cxf>, Vec<const cxf>,
                                     Vec<const cxf>, Vec<cxf>, Vec<cxf>, bool, int);
+template void tile_restrict_2d<double>(hipStream_t, const Op2<double>&, Vec<const cxd>, Vec<const cxd>, Vec<cxd>, int);
+template void tile_restrict_2d<float>(hipStream_t, const Op2<float>&, Vec<const cxf>, Vec<const cxf>, Vec<cxf>, int);
 template bool tile_pre_2d<double>(hipStream_t, const Op2<double>&, const Op2<double>&, double,
                                   Vec<const cxd>, Vec<const cxd>, Vec<cxd>, Vec<const cxd>, Vec<cxd>,
                                   Vec<cxd>, int);

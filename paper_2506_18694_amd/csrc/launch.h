@@ -87,6 +87,9 @@ void stream_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<c
 template <typename T>
 bool tile_sweeps_2d(hipStream_t st, const Op2<T>& L, int S, Vec<const cx<T>> Xin, Vec<const cx<T>> Ec,
                     Vec<const cx<T>> B, Vec<cx<T>> Xout, Vec<cx<T>> Bc, bool update, int ns);
+// b_c = P^T (b - L x), any launch size (no Dirichlet faces)
+template <typename T>
+void tile_restrict_2d(hipStream_t st, const Op2<T>& L, Vec<const cx<T>> X, Vec<const cx<T>> B, Vec<cx<T>> Bc, int ns);
 template <typename T>
 bool tile_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<const cx<T>> U,
                  Vec<const cx<T>> R, Vec<cx<T>> Rho, Vec<const cx<T>> B, Vec<cx<T>> X, Vec<cx<T>> Bc,
@@ -114,6 +117,30 @@ struct SmallCycle {
 template <typename T>
 void vcycle_small(hipStream_t st, const SmallCycle<T>& sc, size_t lds_bytes, const cxd* Ainv,
                   int nc, Vec<const cx<T>> B, Vec<cx<T>> X, int ns);
+
+// ---- GMRES smoothing on 2D levels (kernels2d_gmres.hip) -------------------
+// x = m iterations of Jacobi-left-preconditioned GMRES for L x = b from x
+// (guess) or from 0; L carries the Jacobi factors of omega = 1.
+constexpr int GMRES_ONE_ITS = 5;    // most iterations of the one-workgroup form
+constexpr int GMRES_MAX_ITS = 20;   // most iterations
+constexpr int GMRES_BLOCK = 512;    // nodes per workgroup of the other one
+// in one workgroup per column; false (and nothing launched) for more than
+// 2560 nodes or more than GMRES_ONE_ITS iterations
+bool gmres_one_2d(hipStream_t st, const Op2<double>& L, int m, Vec<const cxd> B, Vec<cxd> X, bool guess, int ns);
+// in 3 m + 2 launches.  Per slot: m + 1 Krylov vectors (basis, bstride apart),
+// m columns of m + 1 Hessenberg entries, m + 1 norms, and per workgroup (nblk
+// = nodes / GMRES_BLOCK, rounded up) m + 1 partial sums in each of part[0],
+// part[1] and one in npart.
+struct GmresWs {
+    cxd* basis;
+    long long bstride;
+    cxd* hess;
+    double* norms;
+    cxd* part[2];
+    double* npart;
+    int m, nblk;
+};
+void gmres_2d(hipStream_t st, const Op2<double>& L, Vec<const cxd> B, Vec<cxd> X, bool guess, const GmresWs& g, int ns);
 
 // ---- 3D Q1 stencils (kernels3d.hip) ---------------------------------------
 // tiled: levels n >= 128 run the z-marching column-tile kernel for the

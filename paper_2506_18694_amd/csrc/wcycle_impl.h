@@ -19,7 +19,8 @@ void pmode(helm_t* h, int l, int mode, Vec<const cxd> X, Vec<const cxd> B, Vec<c
 // Krylov basis of D^{-1} L from r = D^{-1}(b - L x) by Arnoldi with
 // classical Gram-Schmidt applied twice, the (m+1) x m least-squares
 // problem solved on the device, x += V y.  Every column works in its own
-// slot; nothing is read back to the host.
+// slot; nothing is read back to the host.  2D levels run fused kernels, 3D
+// levels one operation per launch.
 void gmres_smooth(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const cxd> b, Vec<cxd> x,
                   bool guess, int ns) {
     hipStream_t st = h->stream;
@@ -35,6 +36,14 @@ void gmres_smooth(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const cxd> b
     double* npart = reinterpret_cast<double*>(w + Lw.gnpart);
     const long long cs = (long long)(m + 1) * N;  // slot stride of the basis
     const int hs = m * (m + 1);                    // slot stride of the Hessenberg
+    if (h->dim == 2) {
+        const Op2<double> L = make_op2<double>(h->coef(HELM_OP_L), h->nl[l], 1.0);
+        if (gmres_one_2d(st, L, m, b, x, guess, ns)) return;
+        const GmresWs g{G, cs, hu, hn, {part, reinterpret_cast<cxd*>(w + Lw.gpart2)}, npart, m,
+                        (int)((N + GMRES_BLOCK - 1) / GMRES_BLOCK)};
+        gmres_2d(st, L, b, x, guess, g, ns);
+        return;
+    }
     const int nblk = multidot_blocks(N);
     auto basis = [&](int i) { return Vec<cxd>{G + (long long)i * N, cs, 0, nullptr}; };
     const Vec<const cxd> V{G, cs, 0, nullptr};
