@@ -1110,8 +1110,10 @@ void vcycle_entry(helm_t* h, const Layout& Lw, void* ws, const void* b, void* x,
         }
     }
     if (fused2d(h) || fused3d(h)) {
-        Vec<cx<T>> r = h->dim == 2 ? vcycle2d_zero<T>(h, Lw, ws, 0, bv, xv, tv, ns)
-                                   : vcycle3d_zero<T>(h, Lw, ws, 0, bv, xv, tv, ns);
+        // the fused cycles leave their result in the second buffer (a single
+        // level and the one-pass-per-launch cycle in the first)
+        Vec<cx<T>> r = h->dim == 2 ? vcycle2d_zero<T>(h, Lw, ws, 0, bv, tv, xv, ns)
+                                   : vcycle3d_zero<T>(h, Lw, ws, 0, bv, tv, xv, ns);
         if (r.base != xv.base) copy_cast<T, T>(h->stream, N, cst(r), xv, ns);
     } else {
         vcycle<T>(h, Lw, ws, 0, bv, xv, tv, ns);
