@@ -46,6 +46,31 @@ void hss_step_mixed(helm_t* h, const Layout& Lw, void* ws, int ns, int s) {
     const zd sa = -km * nu, sb = km * c;
     mixed_nodes<T, T>(h->stream, make_op2<T>(comb, h->n, h->omega), tocx<T>(sb), tocx<T>(sa),
                       mk((T)-1, (T)0), cst(U), cst(R), cst(G), rho, ns);
+    if (use_stream(h, 0) && h->levels > 1) {
+        // the primal step's cycles: the zero-guess pre-smoothing with the
+        // restriction, then per cycle one pass of its post-smoothing and the
+        // next one's pre-smoothing and restriction, the last post-smoothing
+        // added into u, or written at step 0 (per cycle one pass of 14 us at 512^2 instead of the
+        // pre-smoothing, the post-smoothing, the update and the residual, 24)
+        const Op2<T> L = make_op2<T>(lm, h->n, h->omega);
+        const long long N1 = h->Nl[1];
+        Vec<cx<T>> b1 = at_ws<cx<T>>(ws, Lw.mg_b[1], N1);
+        Vec<cx<T>> x1 = at_ws<cx<T>>(ws, Lw.mg_x[1], N1);
+        Vec<cx<T>> t1 = at_ws<cx<T>>(ws, Lw.mg_t[1], N1);
+        const Vec<const cx<T>> none{};
+        stream_pre_2d<T>(h->stream, L, L, (T)0, none, none, Vec<cx<T>>{}, cst(rho), e, b1, ns);
+        for (int q = 0; q < h->cycles; ++q) {
+            const Vec<const cx<T>> ec = cst(vcycle2d_zero<T>(h, Lw, ws, 1, cst(b1), x1, t1, ns));
+            if (q + 1 == h->cycles) {
+                STREAMCHK(stream_sweeps_2d<T>(h->stream, L, 2, cst(e), ec, cst(rho), U, Vec<cx<T>>{}, s > 0, ns));
+            } else {
+                STREAMCHK(stream_sweeps_2d<T>(h->stream, L, 4, cst(e), ec, cst(rho), t, b1, false, ns));
+                std::swap(e, t);
+            }
+        }
+        mixed_sigma<T>(h->stream, h->n, tocx<T>(1.0 / km), cst(U), cst(G), U, ns);
+        return;
+    }
     // q cycles x <- x + V(rho - Lmix x) from x = 0, each added into u as it
     // comes: a zero-guess cycle with the streaming kernels on the current
     // residual, whose update rho - Lmix d is formed out of place; the
