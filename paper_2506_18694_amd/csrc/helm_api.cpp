@@ -614,6 +614,19 @@ inline bool use_stream(const helm_t* h, int l) {
     return h->dim == 2 && !h->opts.no_stream && h->nl[l] >= 16;
 }
 
+// Whether levels l and l + 1 take their pre-smoothing together and their
+// post-smoothing together (one launch each while the launch is small): an
+// even number of streaming levels is left from l on, so that the pairs end at
+// the small-level kernel or the coarsest mesh and of an odd number the finest
+// stays alone, where a pair saves least.
+template <typename T>
+bool pair_levels(const helm_t* h, int l) {
+    const int small = small_start<T>(h);
+    int e = l;  // first level that does not stream
+    while (e < h->levels - 1 && e != small && use_stream(h, e)) ++e;
+    return (e - l) % 2 == 0;
+}
+
 // 2D handles that run the fused HSS step (with Dirichlet faces only where
 // the finest level streams: the streaming kernels clear the faces
 // themselves, the LDS-tiled ones do not)
@@ -626,7 +639,8 @@ inline bool fused2d(const helm_t* h) {
 // level's work buffers; returns the buffer holding the result (x or t).
 // Per level: one kernel for the zero-guess pre-smoothing and the residual
 // restriction, the coarser levels, one kernel for prolongation and the
-// post-smoothing; the small levels run as one LDS-resident kernel.
+// post-smoothing, or two levels at a time in one each (pair_levels); the small
+// levels run as one LDS-resident kernel.
 template <typename T>
 Vec<cx<T>> vcycle2d_zero(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const cx<T>> b,
                          Vec<cx<T>> x, Vec<cx<T>> t, int ns) {
@@ -649,6 +663,24 @@ Vec<cx<T>> vcycle2d_zero(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const
     Vec<cx<T>> xc = at_ws<cx<T>>(ws, Lw.mg_x[l + 1], Nc);
     Vec<cx<T>> tc = at_ws<cx<T>>(ws, Lw.mg_t[l + 1], Nc);
     if (use_stream(h, l)) {
+        if (pair_levels<T>(h, l)) {
+            const Op2<T> Lc = make_op2<T>(h->coef(HELM_OP_L), h->nl[l + 1], h->omega, h->dir);
+            const long long Ncc = h->Nl[l + 2];
+            Vec<cx<T>> bcc = at_ws<cx<T>>(ws, Lw.mg_b[l + 2], Ncc);
+            Vec<cx<T>> xcc = at_ws<cx<T>>(ws, Lw.mg_x[l + 2], Ncc);
+            Vec<cx<T>> tcc = at_ws<cx<T>>(ws, Lw.mg_t[l + 2], Ncc);
+            const Vec<const cx<T>> none{};
+            if (!tile_pre_pair_2d<T>(h->stream, L, Lc, b, x, bc, xc, bcc, ns)) {
+                stream_pre_2d<T>(h->stream, L, L, (T)0, none, none, Vec<cx<T>>{}, b, x, bc, ns);
+                stream_pre_2d<T>(h->stream, Lc, Lc, (T)0, none, none, Vec<cx<T>>{}, cst(bc), xc, bcc, ns);
+            }
+            const Vec<const cx<T>> ecc = cst(vcycle2d_zero<T>(h, Lw, ws, l + 2, cst(bcc), xcc, tcc, ns));
+            if (!tile_post_pair_2d<T>(h->stream, L, Lc, cst(x), b, cst(xc), cst(bc), ecc, t, ns)) {
+                STREAMCHK(stream_sweeps_2d<T>(h->stream, Lc, 2, cst(xc), ecc, cst(bc), tc, Vec<cx<T>>{}, false, ns));
+                STREAMCHK(stream_sweeps_2d<T>(h->stream, L, 2, cst(x), cst(tc), b, t, Vec<cx<T>>{}, false, ns));
+            }
+            return t;
+        }
         stream_pre_2d<T>(h->stream, L, L, (T)0, Vec<const cx<T>>{}, Vec<const cx<T>>{},
                          Vec<cx<T>>{}, b, x, bc, ns);
         Vec<cx<T>> ec = vcycle2d_zero<T>(h, Lw, ws, l + 1, cst(bc), xc, tc, ns);

@@ -111,9 +111,9 @@ __device__ __forceinline__ cx<T> kept(const Node<T>& nd, cx<T> v) {
     return sel(nd.keep, v, zero_cx<T>());
 }
 
-template <typename T, int TW, int TH>
+template <typename T, int TW, int TH, int THREADS = TW * TH>
 __device__ __forceinline__ void clear_rim(Plane<T, TW, TH>& s) {
-    for (int q = threadIdx.x; q < 2 * (TW + 2) + 2 * TH; q += TW * TH) {
+    for (int q = threadIdx.x; q < 2 * (TW + 2) + 2 * TH; q += THREADS) {
         if (q < 2 * (TW + 2)) s[q < TW + 2 ? 0 : TH + 1][q % (TW + 2)] = zero_cx<T>();
         else s[1 + (q - 2 * (TW + 2)) / 2][(q & 1) ? TW + 1 : 0] = zero_cx<T>();
     }
@@ -216,6 +216,135 @@ __global__ __launch_bounds__(TW * TH) void k_tile_pre(Op2<T> L, Op2<T> Bs, T c, 
             kept(nd, restrict_at<T, TW, TH>(pl[0], lx, ly, r));
 }
 
+// Pre-smoothing of two consecutive levels from zero guesses in one launch: on
+// the fine level x, the residual and its restriction b_c; on the coarse one
+// x_c from b_c, and b_cc = P^T (b_c - L_c x_c).  k_tile_pre twice, without the
+// second launch and the trip of b_c through memory.  The coarse pass needs
+// three coarse nodes around the ones it owns and the fine one three fine nodes
+// around those, so a 32 x 32 region owns only 12 x 12 fine nodes: worth it
+// while most compute units would idle.
+constexpr int PAIR = 32, PAIR_C = PAIR / 2;  // fine and coarse nodes of a region's side
+constexpr int PRE2_HALO = 6;                 // coarse nodes before the first owned one
+constexpr int PRE2_OWN = 6;                  // owned coarse nodes (12 fine ones)
+
+template <typename T, bool DIR>
+__global__ __launch_bounds__(PAIR * PAIR) void k_tile_pre2(Op2<T> L, Op2<T> Lc, Vec<const cx<T>> Bv,
+                                                           Vec<cx<T>> X, Vec<cx<T>> Bc, Vec<cx<T>> Xc,
+                                                           Vec<cx<T>> Bcc, TileGrid g) {
+    __shared__ Plane<T, PAIR, PAIR> pl[2];
+    __shared__ Plane<T, PAIR_C, PAIR_C> pc[2];
+    const int slot = (int)blockIdx.x / (g.tx * g.ty), b0 = (int)blockIdx.x % (g.tx * g.ty);
+    const int c0x = (b0 % g.tx) * PRE2_OWN - PRE2_HALO, c0y = (b0 / g.tx) * PRE2_OWN - PRE2_HALO;
+    constexpr int O0 = PRE2_HALO, O1 = PRE2_HALO + PRE2_OWN;  // owned coarse nodes of the region
+    const int tid = (int)threadIdx.x;
+    const int x0 = tid % PAIR, y0 = tid / PAIR, lx = x0 + 1, ly = y0 + 1;
+    const Node<T> nd = node_at<T, DIR>(L, 2 * c0x + x0, 2 * c0y + y0);
+    const long long np = L.n + 1, npc = Lc.n + 1, npcc = Lc.n / 2 + 1, p = (long long)nd.jc * np + nd.ic;
+    cx<T> b = Bv.at(slot)[p];
+    clear_rim<T, PAIR, PAIR>(pl[0]);
+    clear_rim<T, PAIR, PAIR>(pl[1]);
+    clear_rim<T, PAIR_C, PAIR_C, PAIR * PAIR>(pc[0]);
+    clear_rim<T, PAIR_C, PAIR_C, PAIR * PAIR>(pc[1]);
+    if (DIR) b = sel(nd.in && !nd.keep, zero_cx<T>(), b);
+    cx<T> v = kept(nd, nd.jf * b);
+    pl[0][ly][lx] = v;
+    __syncthreads();
+    v = kept(nd, cfma(nd.jf, b - apply_at<T, PAIR, PAIR>(L, pl[0], lx, ly, nd, nd.kc, v), v));
+    if (nd.in && x0 >= 2 * O0 && x0 < 2 * O1 && y0 >= 2 * O0 && y0 < 2 * O1) X.at(slot)[p] = v;
+    pl[1][ly][lx] = v;
+    __syncthreads();
+    pl[0][ly][lx] = kept(nd, b - apply_at<T, PAIR, PAIR>(L, pl[1], lx, ly, nd, nd.kc, v));
+    __syncthreads();
+    // the coarse level: one node per thread of the first four wavefronts
+    const bool act = tid < PAIR_C * PAIR_C;
+    const int cx0 = tid % PAIR_C, cy0 = tid / PAIR_C, cu = cx0 + 1, cv = cy0 + 1;
+    const Node<T> nc = node_at<T, DIR>(Lc, c0x + cx0, c0y + cy0);
+    const bool own = act && nc.in && cx0 >= O0 && cx0 < O1 && cy0 >= O0 && cy0 < O1;
+    const long long pcn = (long long)nc.jc * npc + nc.ic;
+    b = zero_cx<T>();
+    if (act) {
+        b = kept(nc, restrict_at<T, PAIR, PAIR>(pl[0], 2 * cx0 + 1, 2 * cy0 + 1, pl[0][2 * cy0 + 1][2 * cx0 + 1]));
+        if (own) Bc.at(slot)[pcn] = b;
+        v = kept(nc, nc.jf * b);
+        pc[0][cv][cu] = v;
+    }
+    __syncthreads();
+    if (act) {
+        v = kept(nc, cfma(nc.jf, b - apply_at<T, PAIR_C, PAIR_C>(Lc, pc[0], cu, cv, nc, nc.kc, v), v));
+        if (own) Xc.at(slot)[pcn] = v;
+        pc[1][cv][cu] = v;
+    }
+    __syncthreads();
+    cx<T> r = zero_cx<T>();
+    if (act) {
+        r = kept(nc, b - apply_at<T, PAIR_C, PAIR_C>(Lc, pc[1], cu, cv, nc, nc.kc, v));
+        pc[0][cv][cu] = r;
+    }
+    __syncthreads();
+    if (own && !(nc.i & 1) && !(nc.j & 1))
+        Bcc.at(slot)[(long long)(nc.j >> 1) * npcc + (nc.i >> 1)] =
+            kept(nc, restrict_at<T, PAIR_C, PAIR_C>(pc[0], cu, cv, r));
+}
+
+// Post-smoothing of two consecutive levels in one launch: x_c + P e_cc and two
+// sweeps on the coarse level, whose result is used here only (e_c), then
+// x + P e_c and two sweeps on the fine one.  A TW x TH fine region needs the
+// coarse result on the TW / 2 + 1 by TH / 2 + 1 coarse nodes that cover it,
+// and two more on each side to compute it.
+template <typename T, int TW, int TH, bool DIR>
+__global__ __launch_bounds__(TW * TH) void k_tile_post2(Op2<T> L, Op2<T> Lc, Vec<const cx<T>> Xin,
+                                                        Vec<const cx<T>> Bv, Vec<const cx<T>> Xc,
+                                                        Vec<const cx<T>> Bc, Vec<const cx<T>> Ecc,
+                                                        Vec<cx<T>> Xout, TileGrid g) {
+    constexpr int HALO = 2, OW = TW - 2 * HALO, OH = TH - 2 * HALO;
+    constexpr int CW = TW / 2 + 5, CH = TH / 2 + 5;
+    static_assert(CW * CH <= TW * TH && OW % 2 == 0 && OH % 2 == 0, "one coarse node per thread at most");
+    __shared__ Plane<T, TW, TH> pl[2];
+    __shared__ Plane<T, CW, CH> pc[2];
+    const int slot = (int)blockIdx.x / (g.tx * g.ty), b0 = (int)blockIdx.x % (g.tx * g.ty);
+    const int tid = (int)threadIdx.x, x0 = tid % TW, y0 = tid / TW, lx = x0 + 1, ly = y0 + 1;
+    const int fx = (b0 % g.tx) * OW - HALO, fy = (b0 / g.tx) * OH - HALO;  // both even
+    const Node<T> nd = node_at<T, DIR>(L, fx + x0, fy + y0);
+    const bool act = tid < CW * CH;
+    const int cx0 = tid % CW, cy0 = tid / CW, cu = cx0 + 1, cv = cy0 + 1;
+    const Node<T> nc = node_at<T, DIR>(Lc, fx / 2 - 2 + cx0, fy / 2 - 2 + cy0);
+    const long long np = L.n + 1, npc = Lc.n + 1, npcc = Lc.n / 2 + 1, p = (long long)nd.jc * np + nd.ic;
+    cx<T> v = Xin.at(slot)[p];
+    const cx<T> b = Bv.at(slot)[p];
+    cx<T> vc = zero_cx<T>(), bc = zero_cx<T>();
+    if (act) {
+        const long long q = (long long)nc.jc * npc + nc.ic;
+        const long long c0 = (long long)(nc.jc >> 1) * npcc + (nc.ic >> 1);
+        const cx<T>* e = Ecc.at(slot);
+        vc = Xc.at(slot)[q];
+        bc = Bc.at(slot)[q];
+        vc = kept(nc, axpy_real((T)0.5, e[c0] + e[c0 + (nc.ic & 1) + (long long)(nc.jc & 1) * npcc], vc));
+        pc[0][cv][cu] = vc;
+    }
+    clear_rim<T, TW, TH>(pl[0]);
+    clear_rim<T, TW, TH>(pl[1]);
+    clear_rim<T, CW, CH, TW * TH>(pc[0]);
+    clear_rim<T, CW, CH, TW * TH>(pc[1]);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        __syncthreads();
+        if (act) {
+            vc = kept(nc, cfma(nc.jf, bc - apply_at<T, CW, CH>(Lc, pc[s], cu, cv, nc, nc.kc, vc), vc));
+            pc[1 - s][cv][cu] = vc;
+        }
+    }
+    __syncthreads();
+    const int eu = (x0 >> 1) + 3, ev = (y0 >> 1) + 3;
+    v = kept(nd, axpy_real((T)0.5, pc[0][ev][eu] + pc[0][ev + (y0 & 1)][eu + (x0 & 1)], v));
+    pl[0][ly][lx] = v;
+    __syncthreads();
+    v = kept(nd, cfma(nd.jf, b - apply_at<T, TW, TH>(L, pl[0], lx, ly, nd, nd.kc, v), v));
+    pl[1][ly][lx] = v;
+    __syncthreads();
+    v = kept(nd, cfma(nd.jf, b - apply_at<T, TW, TH>(L, pl[1], lx, ly, nd, nd.kc, v), v));
+    if (nd.in && x0 >= HALO && x0 < TW - HALO && y0 >= HALO && y0 < TH - HALO) Xout.at(slot)[p] = v;
+}
+
 constexpr int TW = 32;  // tile columns
 
 inline TileGrid tile_grid(int n, int halo, int th) {
@@ -244,6 +373,16 @@ int tile_height(int n, int halo, int ns, int most16, int most32) {
     if ((long long)g32.tx * g32.ty * ns <= most32) return 32;
     return 0;
 }
+
+// Most workgroups of the two-level passes: the down pass while each has a
+// compute unit to itself, the up pass up to about four per compute unit (its
+// halo is small).  Measured (us per launch, FP64; FP32 in parentheses; the two
+// launches that it replaces, without the 1 us between them):
+//   down  92^2 6.3 (5.0) : 3.8 + 3.7,   128^2 5.9 (5.1) : 4.1 + 4.0,
+//         4 x 92^2 6.6 (5.3) : 4.4 + 3.9,   256^2 (484) 11.3 (9.8) : 4.4 + 4.0
+//   up    92^2 5.4 (4.7) : 3.7 + 3.7,   256^2 5.8 (5.0) : 4.0 + 3.9,
+//         512^2 (817) 10.0 (8.0) : 6.5 + 4.0,   8 x 176^2 (1560) 15.4 : 9.0 + 6.0
+constexpr int PRE2_MOST = 256, POST2_MOST = 1024;
 
 }  // namespace
 
@@ -308,6 +447,31 @@ bool tile_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<con
     return true;
 }
 
+template <typename T>
+bool tile_pre_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, Vec<const cx<T>> B, Vec<cx<T>> X,
+                      Vec<cx<T>> Bc, Vec<cx<T>> Xc, Vec<cx<T>> Bcc, int ns) {
+    const int t = (L.n / 2 + PRE2_OWN) / PRE2_OWN;
+    const TileGrid g{t, t};
+    if ((long long)t * t * ns > PRE2_MOST) return false;
+    const unsigned nb = (unsigned)(t * t * ns);
+    if (L.dir) k_tile_pre2<T, true><<<nb, PAIR * PAIR, 0, st>>>(L, Lc, B, X, Bc, Xc, Bcc, g);
+    else k_tile_pre2<T, false><<<nb, PAIR * PAIR, 0, st>>>(L, Lc, B, X, Bc, Xc, Bcc, g);
+    return true;
+}
+
+template <typename T>
+bool tile_post_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, Vec<const cx<T>> X,
+                       Vec<const cx<T>> B, Vec<const cx<T>> Xc, Vec<const cx<T>> Bc, Vec<const cx<T>> Ecc,
+                       Vec<cx<T>> Xout, int ns) {
+    constexpr int TH = 16;
+    const TileGrid g = tile_grid(L.n, 2, TH);
+    if ((long long)g.tx * g.ty * ns > POST2_MOST) return false;
+    const unsigned nb = (unsigned)(g.tx * g.ty * ns);
+    if (L.dir) k_tile_post2<T, TW, TH, true><<<nb, TW * TH, 0, st>>>(L, Lc, X, B, Xc, Bc, Ecc, Xout, g);
+    else k_tile_post2<T, TW, TH, false><<<nb, TW * TH, 0, st>>>(L, Lc, X, B, Xc, Bc, Ecc, Xout, g);
+    return true;
+}
+
 template bool tile_sweeps_2d<double>(hipStream_t, const Op2<double>&, int, Vec<const cxd>, Vec<const cxd>,
                                      Vec<const cxd>, Vec<cxd>, Vec<cxd>, bool, int);
 template bool tile_sweeps_2d<float>(hipStream_t, const Op2<float>&, int, Vec<const cxf>, Vec<const cxf>,
@@ -319,5 +483,14 @@ template bool tile_pre_2d<double>(hipStream_t, const Op2<double>&, const Op2<dou
                                   Vec<cxd>, int);
 template bool tile_pre_2d<float>(hipStream_t, const Op2<float>&, const Op2<float>&, float, Vec<const cxf>,
                                  Vec<const cxf>, Vec<cxf>, Vec<const cxf>, Vec<cxf>, Vec<cxf>, int);
+
+template bool tile_pre_pair_2d<double>(hipStream_t, const Op2<double>&, const Op2<double>&, Vec<const cxd>, Vec<cxd>, Vec<cxd>,
+                                      Vec<cxd>, Vec<cxd>, int);
+template bool tile_post_pair_2d<double>(hipStream_t, const Op2<double>&, const Op2<double>&, Vec<const cxd>, Vec<const cxd>,
+                                       Vec<const cxd>, Vec<const cxd>, Vec<const cxd>, Vec<cxd>, int);
+template bool tile_pre_pair_2d<float>(hipStream_t, const Op2<float>&, const Op2<float>&, Vec<const cxf>, Vec<cxf>, Vec<cxf>,
+                                      Vec<cxf>, Vec<cxf>, int);
+template bool tile_post_pair_2d<float>(hipStream_t, const Op2<float>&, const Op2<float>&, Vec<const cxf>, Vec<const cxf>,
+                                       Vec<const cxf>, Vec<const cxf>, Vec<const cxf>, Vec<cxf>, int);
 
 }  // namespace helm

@@ -95,6 +95,19 @@ bool tile_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<con
                  Vec<const cx<T>> R, Vec<cx<T>> Rho, Vec<const cx<T>> B, Vec<cx<T>> X, Vec<cx<T>> Bc,
                  int ns);
 
+// Two consecutive levels (L, and Lc on the mesh of half the cells) per launch;
+// false, and nothing launched, when the launch is too large for it.
+// Down: x from zero and b_c = P^T (b - L x) on L, x_c from zero and
+// b_cc = P^T (b_c - L_c x_c) on Lc.  Up: x_c + P e_cc and two sweeps on Lc
+// (not written), whose result corrects x before two sweeps on L, written.
+template <typename T>
+bool tile_pre_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, Vec<const cx<T>> B, Vec<cx<T>> X,
+                      Vec<cx<T>> Bc, Vec<cx<T>> Xc, Vec<cx<T>> Bcc, int ns);
+template <typename T>
+bool tile_post_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, Vec<const cx<T>> X,
+                       Vec<const cx<T>> B, Vec<const cx<T>> Xc, Vec<const cx<T>> Bc, Vec<const cx<T>> Ecc,
+                       Vec<cx<T>> Xout, int ns);
+
 // ---- small-level V-cycle in LDS (kernels2d_small.hip) ---------------------
 // Levels 0..nlev-1 of this record are consecutive mesh levels; the last is
 // the coarsest (solved with the dense FP64 inverse).  Offsets are in
