@@ -2,6 +2,8 @@
 // boundary: Arnoldi inner products (deterministic two-stage reductions with
 // wavefront shuffles), basis updates, norms, precision casts, and the dense
 // FP64 coarsest-mesh solve.
+#include <algorithm>
+
 #include "launch.h"
 #include "faces.h"
 
@@ -137,7 +139,10 @@ __global__ __launch_bounds__(BS) void k_real_to_complex(long long N, const doubl
 // ---- Arnoldi reductions -------------------------------------------------------
 // part[(slot * m + i) * nblk + blk] = sum over the block's nodes of conj(V_i) w;
 // with wpart, also wpart[slot * nblk + blk] = the block's sum of |w|^2; with
-// flag, slots whose flag is 0 are skipped
+// flag, slots whose flag is 0 are skipped.  A group's loads and its sum over
+// the block form one chain of about 2 us, so a mesh whose nodes are few blocks
+// spreads the groups over blockIdx.y as well (each reads w again); the sums do
+// not depend on how many there are.
 __global__ __launch_bounds__(BS) void k_multidot(long long N, int m, const int* mlen,
                                                  Vec<const cxd> V, Vec<const cxd> W, cxd* part,
                                                  unsigned nblk, double* wpart, const int* flag) {
@@ -155,7 +160,7 @@ __global__ __launch_bounds__(BS) void k_multidot(long long N, int m, const int* 
         wv[q] = t < N ? w[t] : mk(0.0, 0.0);
     }
     const int ms = mlen ? mlen[slot] : m;  // this slot's vector count (<= m)
-    for (int i0 = 0; i0 < ms; i0 += GROUP) {
+    for (int i0 = (int)blockIdx.y * GROUP; i0 < ms; i0 += (int)gridDim.y * GROUP) {
         double acc[2 * GROUP];
 #pragma unroll
         for (int c = 0; c < 2 * GROUP; ++c) acc[c] = 0.0;
@@ -182,7 +187,7 @@ __global__ __launch_bounds__(BS) void k_multidot(long long N, int m, const int* 
                     part[((long long)slot * m + i0 + u) * nblk + blk] = mk(acc[2 * u], acc[2 * u + 1]);
         }
     }
-    if (wpart) {
+    if (wpart && blockIdx.y == 0) {
         double acc[1] = {0.0};
 #pragma unroll
         for (int q = 0; q < NPT; ++q) acc[0] += wv[q].x * wv[q].x + wv[q].y * wv[q].y;
@@ -404,8 +409,11 @@ void real_to_complex(hipStream_t st, long long N, const double* f, cxd* b, int n
 
 void multidot(hipStream_t st, long long N, int m, const int* mlen, Vec<const cxd> V,
               Vec<const cxd> W, cxd* part, int nslots, double* wpart, const int* flag) {
-    const unsigned nblk = multidot_blocks(N);
-    k_multidot<<<nblk * nslots, BS, 0, st>>>(N, m, mlen, V, W, part, nblk, wpart, flag);
+    // up to 2048 blocks (eight per compute unit): 17 blocks x 6 columns with 100
+    // vectors took 50 us as 102 blocks
+    const unsigned nblk = multidot_blocks(N), groups = (unsigned)(m + GROUP - 1) / GROUP;
+    const unsigned gy = std::max(1u, std::min(groups, 2048u / (nblk * nslots)));
+    k_multidot<<<dim3(nblk * nslots, gy), BS, 0, st>>>(N, m, mlen, V, W, part, nblk, wpart, flag);
 }
 
 void reduce_parts(hipStream_t st, int m, const int* mlen, int nblk, const cxd* part, cxd* out,
