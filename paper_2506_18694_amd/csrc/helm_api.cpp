@@ -675,7 +675,7 @@ Vec<cx<T>> vcycle2d_zero(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const
                 stream_pre_2d<T>(h->stream, Lc, Lc, (T)0, none, none, Vec<cx<T>>{}, cst(bc), xc, bcc, ns);
             }
             const Vec<const cx<T>> ecc = cst(vcycle2d_zero<T>(h, Lw, ws, l + 2, cst(bcc), xcc, tcc, ns));
-            if (!tile_post_pair_2d<T>(h->stream, L, Lc, cst(x), b, cst(xc), cst(bc), ecc, t, ns)) {
+            if (!tile_post_pair_2d<T>(h->stream, L, Lc, 2, cst(x), b, cst(xc), cst(bc), ecc, t, Vec<cx<T>>{}, false, ns)) {
                 STREAMCHK(stream_sweeps_2d<T>(h->stream, Lc, 2, cst(xc), ecc, cst(bc), tc, Vec<cx<T>>{}, false, ns));
                 STREAMCHK(stream_sweeps_2d<T>(h->stream, L, 2, cst(x), cst(tc), b, t, Vec<cx<T>>{}, false, ns));
             }
@@ -691,6 +691,49 @@ Vec<cx<T>> vcycle2d_zero(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const
     Vec<cx<T>> ec = vcycle2d_zero<T>(h, Lw, ws, l + 1, cst(bc), xc, tc, ns);
     sweeps_2d<T>(h->stream, L, 2, cst(x), cst(ec), b, t, false, ns);
     return t;
+}
+
+// The rest of a streaming 2D cycle once the finest level's pre-smoothing has
+// left x and the restricted residual b1: the coarser levels, then the finest
+// level's post-smoothing of rho's system.  S = 2: into out, or added into it
+// (update); S = 4: two more sweeps, the next cycle's pre-smoothing, into out,
+// and the next b1.  An odd number of streaming levels below the finest leaves
+// level 1 without a partner (pair_levels): while the launches are small its
+// post-smoothing shares the finest level's, with the next b1 in the buffer that
+// its result would have taken (the two swap).  marks: time the finest level's
+// launch; returns the complex values per node that it moves.
+template <typename T>
+double cycle_rest2d(helm_t* h, const Layout& Lw, void* ws, const Op2<T>& L, int S, Vec<const cx<T>> x,
+                    Vec<const cx<T>> rho, Vec<cx<T>> out, bool update, Vec<cx<T>>& b1, Vec<cx<T>> x1,
+                    Vec<cx<T>>& t1, int ns, bool marks) {
+    const Vec<const cx<T>> none{};
+    const Vec<cx<T>> nil{};
+    const double passes = S == 4 ? 3.5 : (update ? 4.25 : 3.25);
+    Vec<const cx<T>> ec;
+    if (h->levels > 2 && small_start<T>(h) != 1 && use_stream(h, 1) && !pair_levels<T>(h, 1)) {
+        const Op2<T> L1 = make_op2<T>(h->coef(HELM_OP_L), h->nl[1], h->omega, h->dir);
+        const long long N2 = h->Nl[2];
+        Vec<cx<T>> b2 = at_ws<cx<T>>(ws, Lw.mg_b[2], N2);
+        stream_pre_2d<T>(h->stream, L1, L1, (T)0, none, none, nil, cst(b1), x1, b2, ns);
+        const Vec<const cx<T>> ecc = cst(vcycle2d_zero<T>(h, Lw, ws, 2, cst(b2), at_ws<cx<T>>(ws, Lw.mg_x[2], N2),
+                                                          at_ws<cx<T>>(ws, Lw.mg_t[2], N2), ns));
+        if (marks) h->prof_mark();
+        if (tile_post_pair_2d<T>(h->stream, L, L1, S, x, rho, cst(x1), cst(b1), ecc, out, S == 4 ? t1 : nil,
+                                 update, ns)) {
+            if (marks) h->prof_mark();
+            if (S == 4) std::swap(b1, t1);
+            return passes + 0.3125;
+        }
+        if (marks && h->prof_used > 0) --h->prof_used;
+        STREAMCHK(stream_sweeps_2d<T>(h->stream, L1, 2, cst(x1), ecc, cst(b1), t1, nil, false, ns));
+        ec = cst(t1);
+    } else {
+        ec = cst(vcycle2d_zero<T>(h, Lw, ws, 1, cst(b1), x1, t1, ns));
+    }
+    if (marks) h->prof_mark();
+    STREAMCHK(stream_sweeps_2d<T>(h->stream, L, S, x, ec, rho, out, S == 4 ? b1 : nil, update, ns));
+    if (marks) h->prof_mark();
+    return passes;
 }
 
 // One shifted-HSS step s with fused 2D kernels: the residual
@@ -727,29 +770,27 @@ void hss_step2d(helm_t* h, const Layout& Lw, void* ws, int ns, int s) {
     else hss_pre0r_2d<T>(h->stream, L, Bs, c, uin, cst(R), rho, xa, b1, ns);
     Vec<cx<T>> x = xa, t = xb;
     for (int q = 0; q < h->cycles; ++q) {
-        if (q > 0 && !streaming) resid_restrict2d<T>(h->stream, L, cst(x), cst(rho), b1, ns);
-        Vec<const cx<T>> ec = cst(vcycle2d_zero<T>(h, Lw, ws, 1, cst(b1), x1, t1, ns));
         const bool last = q == h->cycles - 1;
         // the profiled kernel is the four-sweep pass (the single two-sweep
         // update pass when only one cycle is used)
         const bool prof = h->prof_on && (h->cycles == 1 || !last) && s % helm_s::PROF_EVERY == 0;
-        if (prof) h->prof_mark();
-        if (last) {
-            if (streaming) STREAMCHK(stream_sweeps_2d<T>(h->stream, L, 2, cst(x), ec, cst(rho), u, Vec<cx<T>>{}, s > 0, ns));
-            else sweeps_2d<T>(h->stream, L, 2, cst(x), ec, cst(rho), u, s > 0, ns);
+        // algorithmic bytes: x, b and e_c (a quarter vector) read, x'
+        // written, and with the streaming pass b_c (a quarter vector)
+        // written; the update pass reads and writes u instead
+        double passes;
+        if (streaming) {
+            passes = cycle_rest2d<T>(h, Lw, ws, L, last ? 2 : 4, cst(x), cst(rho), last ? u : t, last && s > 0, b1,
+                                     x1, t1, ns, prof);
         } else {
-            if (streaming) STREAMCHK(stream_sweeps_2d<T>(h->stream, L, 4, cst(x), ec, cst(rho), t, b1, false, ns));
-            else sweeps_2d<T>(h->stream, L, 4, cst(x), ec, cst(rho), t, false, ns);
-            std::swap(x, t);
+            if (q > 0) resid_restrict2d<T>(h->stream, L, cst(x), cst(rho), b1, ns);
+            Vec<const cx<T>> ec = cst(vcycle2d_zero<T>(h, Lw, ws, 1, cst(b1), x1, t1, ns));
+            if (prof) h->prof_mark();
+            sweeps_2d<T>(h->stream, L, last ? 2 : 4, cst(x), ec, cst(rho), last ? u : t, last && s > 0, ns);
+            if (prof) h->prof_mark();
+            passes = last && s > 0 ? 4.25 : 3.25;
         }
-        if (prof) {
-            h->prof_mark();
-            // algorithmic bytes: x, b and e_c (a quarter vector) read, x'
-            // written, and with the streaming pass b_c (a quarter vector)
-            // written; the update pass reads and writes u instead
-            const double passes = last ? (s > 0 ? 4.25 : 3.25) : (streaming ? 3.5 : 3.25);
-            h->prof_pending_bytes += sizeof(cx<T>) * (double)N * ns * passes;
-        }
+        if (!last) std::swap(x, t);
+        if (prof) h->prof_pending_bytes += sizeof(cx<T>) * (double)N * ns * passes;
     }
 }
 

@@ -288,29 +288,36 @@ __global__ __launch_bounds__(PAIR * PAIR) void k_tile_pre2(Op2<T> L, Op2<T> Lc, 
 
 // Post-smoothing of two consecutive levels in one launch: x_c + P e_cc and two
 // sweeps on the coarse level, whose result is used here only (e_c), then
-// x + P e_c and two sweeps on the fine one.  A TW x TH fine region needs the
-// coarse result on the TW / 2 + 1 by TH / 2 + 1 coarse nodes that cover it,
-// and two more on each side to compute it.
-template <typename T, int TW, int TH, bool DIR>
+// x + P e_c and S sweeps on the fine one, written or added into u (UPDATE),
+// and with RESID b_c = P^T (b - L x) into Bcout, another buffer than Bc, which
+// other workgroups still read.  A TW x TH fine region needs the coarse result
+// on the TW / 2 + 1 by TH / 2 + 1 coarse nodes that cover it, and two more on
+// each side to compute it.
+template <typename T, int TW, int TH, int S, bool RESID, bool UPDATE, bool DIR>
 __global__ __launch_bounds__(TW * TH) void k_tile_post2(Op2<T> L, Op2<T> Lc, Vec<const cx<T>> Xin,
                                                         Vec<const cx<T>> Bv, Vec<const cx<T>> Xc,
                                                         Vec<const cx<T>> Bc, Vec<const cx<T>> Ecc,
-                                                        Vec<cx<T>> Xout, TileGrid g) {
-    constexpr int HALO = 2, OW = TW - 2 * HALO, OH = TH - 2 * HALO;
+                                                        Vec<cx<T>> Xout, Vec<cx<T>> Bcout, TileGrid g) {
+    constexpr int HALO = S + (RESID ? 2 : 0), OW = TW - 2 * HALO, OH = TH - 2 * HALO;
     constexpr int CW = TW / 2 + 5, CH = TH / 2 + 5;
-    static_assert(CW * CH <= TW * TH && OW % 2 == 0 && OH % 2 == 0, "one coarse node per thread at most");
+    static_assert(CW * CH <= TW * TH, "one coarse node per thread at most");
+    static_assert(HALO % 2 == 0 && OW > 0 && OH > 0 && OW % 2 == 0 && OH % 2 == 0, "even regions");
     __shared__ Plane<T, TW, TH> pl[2];
     __shared__ Plane<T, CW, CH> pc[2];
     const int slot = (int)blockIdx.x / (g.tx * g.ty), b0 = (int)blockIdx.x % (g.tx * g.ty);
     const int tid = (int)threadIdx.x, x0 = tid % TW, y0 = tid / TW, lx = x0 + 1, ly = y0 + 1;
     const int fx = (b0 % g.tx) * OW - HALO, fy = (b0 / g.tx) * OH - HALO;  // both even
     const Node<T> nd = node_at<T, DIR>(L, fx + x0, fy + y0);
+    const bool own = nd.in && x0 >= HALO && x0 < TW - HALO && y0 >= HALO && y0 < TH - HALO;
     const bool act = tid < CW * CH;
     const int cx0 = tid % CW, cy0 = tid / CW, cu = cx0 + 1, cv = cy0 + 1;
     const Node<T> nc = node_at<T, DIR>(Lc, fx / 2 - 2 + cx0, fy / 2 - 2 + cy0);
     const long long np = L.n + 1, npc = Lc.n + 1, npcc = Lc.n / 2 + 1, p = (long long)nd.jc * np + nd.ic;
     cx<T> v = Xin.at(slot)[p];
     const cx<T> b = Bv.at(slot)[p];
+    cx<T>* xo = Xout.at(slot);
+    cx<T> uo = zero_cx<T>();
+    if (UPDATE) uo = xo[p];
     cx<T> vc = zero_cx<T>(), bc = zero_cx<T>();
     if (act) {
         const long long q = (long long)nc.jc * npc + nc.ic;
@@ -337,12 +344,22 @@ __global__ __launch_bounds__(TW * TH) void k_tile_post2(Op2<T> L, Op2<T> Lc, Vec
     const int eu = (x0 >> 1) + 3, ev = (y0 >> 1) + 3;
     v = kept(nd, axpy_real((T)0.5, pc[0][ev][eu] + pc[0][ev + (y0 & 1)][eu + (x0 & 1)], v));
     pl[0][ly][lx] = v;
-    __syncthreads();
-    v = kept(nd, cfma(nd.jf, b - apply_at<T, TW, TH>(L, pl[0], lx, ly, nd, nd.kc, v), v));
-    pl[1][ly][lx] = v;
-    __syncthreads();
-    v = kept(nd, cfma(nd.jf, b - apply_at<T, TW, TH>(L, pl[1], lx, ly, nd, nd.kc, v), v));
-    if (nd.in && x0 >= HALO && x0 < TW - HALO && y0 >= HALO && y0 < TH - HALO) Xout.at(slot)[p] = v;
+#pragma unroll
+    for (int s = 1; s <= S; ++s) {
+        __syncthreads();
+        v = kept(nd, cfma(nd.jf, b - apply_at<T, TW, TH>(L, pl[(s - 1) & 1], lx, ly, nd, nd.kc, v), v));
+        if (s < S || RESID) pl[s & 1][ly][lx] = v;
+    }
+    if (own) xo[p] = UPDATE ? uo + v : v;
+    if constexpr (RESID) {
+        __syncthreads();
+        const cx<T> r = kept(nd, b - apply_at<T, TW, TH>(L, pl[S & 1], lx, ly, nd, nd.kc, v));
+        pl[(S + 1) & 1][ly][lx] = r;
+        __syncthreads();
+        if (own && !(nd.i & 1) && !(nd.j & 1))
+            Bcout.at(slot)[(long long)(nd.j >> 1) * npc + (nd.i >> 1)] =
+                kept(nd, restrict_at<T, TW, TH>(pl[(S + 1) & 1], lx, ly, r));
+    }
 }
 
 constexpr int TW = 32;  // tile columns
@@ -383,6 +400,12 @@ int tile_height(int n, int halo, int ns, int most16, int most32) {
 //   up    92^2 5.4 (4.7) : 3.7 + 3.7,   256^2 5.8 (5.0) : 4.0 + 3.9,
 //         512^2 (817) 10.0 (8.0) : 6.5 + 4.0,   8 x 176^2 (1560) 15.4 : 9.0 + 6.0
 constexpr int PRE2_MOST = 256, POST2_MOST = 1024;
+// With the finest level's four-sweep pass, 32 rows up to 400 workgroups (16 as
+// that pass alone):
+//   128^2 (231, FP32) 6.0 : 4.2 + 3.3,   256^2 (169) 8.6 (7.2) : 7.0 + 3.9 (5.7 + 3.3),
+//   2 x 256^2 (338) 14.2 (10.9) : 11.5 + 4.0 (7.9 + 3.5),
+//   512^2 (676) 20.2 (15.8) : 15.8 + 4.0 (10.7 + 4.0)
+constexpr int POST4_MOST16 = 256, POST4_MOST32 = 400;
 
 }  // namespace
 
@@ -460,15 +483,24 @@ bool tile_pre_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, Vec<con
 }
 
 template <typename T>
-bool tile_post_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, Vec<const cx<T>> X,
+bool tile_post_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, int S, Vec<const cx<T>> X,
                        Vec<const cx<T>> B, Vec<const cx<T>> Xc, Vec<const cx<T>> Bc, Vec<const cx<T>> Ecc,
-                       Vec<cx<T>> Xout, int ns) {
-    constexpr int TH = 16;
-    const TileGrid g = tile_grid(L.n, 2, TH);
-    if ((long long)g.tx * g.ty * ns > POST2_MOST) return false;
+                       Vec<cx<T>> Xout, Vec<cx<T>> Bcout, bool update, int ns) {
+    const bool s4 = S == 4;  // with the restriction
+    const int th = s4 ? tile_height(L.n, 6, ns, POST4_MOST16, POST4_MOST32) : tile_height(L.n, 2, ns, POST2_MOST, 0);
+    if (th == 0) return false;
+    const TileGrid g = tile_grid(L.n, s4 ? 6 : 2, th);
     const unsigned nb = (unsigned)(g.tx * g.ty * ns);
-    if (L.dir) k_tile_post2<T, TW, TH, true><<<nb, TW * TH, 0, st>>>(L, Lc, X, B, Xc, Bc, Ecc, Xout, g);
-    else k_tile_post2<T, TW, TH, false><<<nb, TW * TH, 0, st>>>(L, Lc, X, B, Xc, Bc, Ecc, Xout, g);
+#define HELM_POST2(HH, SS, RR, UU)                                                                  \
+    do {                                                                                            \
+        if (L.dir) k_tile_post2<T, TW, HH, SS, RR, UU, true><<<nb, TW * HH, 0, st>>>(L, Lc, X, B, Xc, Bc, Ecc, Xout, Bcout, g); \
+        else k_tile_post2<T, TW, HH, SS, RR, UU, false><<<nb, TW * HH, 0, st>>>(L, Lc, X, B, Xc, Bc, Ecc, Xout, Bcout, g); \
+    } while (0)
+    if (s4 && th == 16) HELM_POST2(16, 4, true, false);
+    else if (s4) HELM_POST2(32, 4, true, false);
+    else if (update) HELM_POST2(16, 2, false, true);
+    else HELM_POST2(16, 2, false, false);
+#undef HELM_POST2
     return true;
 }
 
@@ -486,11 +518,11 @@ template bool tile_pre_2d<float>(hipStream_t, const Op2<float>&, const Op2<float
 
 template bool tile_pre_pair_2d<double>(hipStream_t, const Op2<double>&, const Op2<double>&, Vec<const cxd>, Vec<cxd>, Vec<cxd>,
                                       Vec<cxd>, Vec<cxd>, int);
-template bool tile_post_pair_2d<double>(hipStream_t, const Op2<double>&, const Op2<double>&, Vec<const cxd>, Vec<const cxd>,
-                                       Vec<const cxd>, Vec<const cxd>, Vec<const cxd>, Vec<cxd>, int);
+template bool tile_post_pair_2d<double>(hipStream_t, const Op2<double>&, const Op2<double>&, int, Vec<const cxd>, Vec<const cxd>,
+                                       Vec<const cxd>, Vec<const cxd>, Vec<const cxd>, Vec<cxd>, Vec<cxd>, bool, int);
 template bool tile_pre_pair_2d<float>(hipStream_t, const Op2<float>&, const Op2<float>&, Vec<const cxf>, Vec<cxf>, Vec<cxf>,
                                       Vec<cxf>, Vec<cxf>, int);
-template bool tile_post_pair_2d<float>(hipStream_t, const Op2<float>&, const Op2<float>&, Vec<const cxf>, Vec<const cxf>,
-                                       Vec<const cxf>, Vec<const cxf>, Vec<const cxf>, Vec<cxf>, int);
+template bool tile_post_pair_2d<float>(hipStream_t, const Op2<float>&, const Op2<float>&, int, Vec<const cxf>, Vec<const cxf>,
+                                       Vec<const cxf>, Vec<const cxf>, Vec<const cxf>, Vec<cxf>, Vec<cxf>, bool, int);
 
 }  // namespace helm

@@ -57,11 +57,10 @@ struct StreamGrid {
     unsigned strips, segs, units;
     unsigned edge_units, eblocks;
 };
-StreamGrid stream_grid(int n, int halo, int ns, int H);
 // x_out = S Jacobi sweeps from x_in (+ P e_c when Ec.base is set); with
 // update, x_out += result; when Bc.base is set, also b_c = P^T (b - L x_out)
 // on the n/2 mesh.  Supported: (S, prolong, restrict, update) in
-// {(4,1,1,0), (2,1,0,1), (2,1,0,0), (2,0,1,0), (4,1,0,0), (1,0,0,0)};
+// {(4,1,1,0), (2,1,0,1), (2,1,0,0)};
 // returns false (and launches nothing) for any other.
 template <typename T>
 bool stream_sweeps_2d(hipStream_t st, const Op2<T>& L, int S, Vec<const cx<T>> Xin,
@@ -99,14 +98,16 @@ bool tile_pre_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Bs, T c, Vec<con
 // false, and nothing launched, when the launch is too large for it.
 // Down: x from zero and b_c = P^T (b - L x) on L, x_c from zero and
 // b_cc = P^T (b_c - L_c x_c) on Lc.  Up: x_c + P e_cc and two sweeps on Lc
-// (not written), whose result corrects x before two sweeps on L, written.
+// (not written), whose result corrects x before S sweeps on L: two, written or
+// with update added into Xout, or four, written, with P^T (b - L x) into Bcout
+// (not Bc).
 template <typename T>
 bool tile_pre_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, Vec<const cx<T>> B, Vec<cx<T>> X,
                       Vec<cx<T>> Bc, Vec<cx<T>> Xc, Vec<cx<T>> Bcc, int ns);
 template <typename T>
-bool tile_post_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, Vec<const cx<T>> X,
+bool tile_post_pair_2d(hipStream_t st, const Op2<T>& L, const Op2<T>& Lc, int S, Vec<const cx<T>> X,
                        Vec<const cx<T>> B, Vec<const cx<T>> Xc, Vec<const cx<T>> Bc, Vec<const cx<T>> Ecc,
-                       Vec<cx<T>> Xout, int ns);
+                       Vec<cx<T>> Xout, Vec<cx<T>> Bcout, bool update, int ns);
 
 // ---- small-level V-cycle in LDS (kernels2d_small.hip) ---------------------
 // Levels 0..nlev-1 of this record are consecutive mesh levels; the last is

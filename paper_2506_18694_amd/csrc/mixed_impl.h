@@ -60,13 +60,10 @@ void hss_step_mixed(helm_t* h, const Layout& Lw, void* ws, int ns, int s) {
         const Vec<const cx<T>> none{};
         stream_pre_2d<T>(h->stream, L, L, (T)0, none, none, Vec<cx<T>>{}, cst(rho), e, b1, ns);
         for (int q = 0; q < h->cycles; ++q) {
-            const Vec<const cx<T>> ec = cst(vcycle2d_zero<T>(h, Lw, ws, 1, cst(b1), x1, t1, ns));
-            if (q + 1 == h->cycles) {
-                STREAMCHK(stream_sweeps_2d<T>(h->stream, L, 2, cst(e), ec, cst(rho), U, Vec<cx<T>>{}, s > 0, ns));
-            } else {
-                STREAMCHK(stream_sweeps_2d<T>(h->stream, L, 4, cst(e), ec, cst(rho), t, b1, false, ns));
-                std::swap(e, t);
-            }
+            const bool last = q + 1 == h->cycles;
+            (void)cycle_rest2d<T>(h, Lw, ws, L, last ? 2 : 4, cst(e), cst(rho), last ? U : t, last && s > 0, b1, x1,
+                                  t1, ns, false);
+            if (!last) std::swap(e, t);
         }
         mixed_sigma<T>(h->stream, h->n, tocx<T>(1.0 / km), cst(U), cst(G), U, ns);
         return;

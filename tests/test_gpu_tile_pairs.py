@@ -52,3 +52,24 @@ def test_paired_cycle_matches_the_oracle(n, levels):
     # rounding only; the coarse solves differ by their condition number times it
     assert rel_l2(x[0], ref) < 1e-10
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,levels,faces", [(64, 3, 0), (100, 3, 6), (144, 3, 0), (208, 5, 9)])
+def test_finest_level_shares_the_launch_of_an_odd_one(n, levels, faces, precision):
+    """One (or three) streaming levels below the finest: the odd level's
+    post-smoothing runs in the finest level's four-sweep and update passes, up
+    to 400 and 1024 workgroups."""
+    from paper_2506_18694_amd import Solver
+    g = torch.Generator(device="cuda").manual_seed(n)
+    many = 1024 // (((n // 28) + 1) * (n // 12 + 1)) + 2
+    v = torch.randn(many, (n + 1) ** 2, dtype=torch.complex128, device="cuda", generator=g)
+    for f, at in enumerate(((slice(None), 0), (slice(None), n), (0, slice(None)), (n, slice(None)))):
+        if faces >> f & 1:
+            v.view(many, n + 1, n + 1)[(slice(None),) + at] = 0
+    s = Solver(2, n, levels, n / 6.4, precision=precision, mg_cycles=3, hss_steps=3, restart=1,
+               dirichlet_faces=faces)
+    zs = s.precondition(v)
+    for cols in (1, 3, 400 // (n // 20 + 1) ** 2 + 1):
+        assert torch.equal(s.precondition(v[:cols].contiguous()), zs[:cols])
+    s.close()
