@@ -47,6 +47,9 @@
 #include <mutex>
 #include <tuple>
 #include <type_traits>
+#include <iterator>
+#include <utility>
+#include <vector>
 
 #include "launch.h"
 #include "stencil_rows.h"
@@ -372,6 +375,7 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
     constexpr int DEPTH = S + (RESID ? 2 : 0);  // lag of the deepest stage
     constexpr int HALO = DEPTH;
     constexpr int NR = S + (RESID ? 2 : 0);
+    static_assert(S == 2 || S == 4, "two or four sweeps");
     constexpr int NB = (S + (RESID ? 2 : 1) <= 3) ? 3 : 6;  // queue of b rows
     constexpr int NBUF = 3;    // input rows in flight
     constexpr int CHUNK = NB;  // steps per block: a multiple of 3, NB and NBUF
@@ -395,8 +399,16 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
     const long long np = n + 1, npc = n / 2 + 1;
 
     Ring<T> rg[NR];
-#pragma unroll
-    for (int k = 0; k < NR; ++k) ring_clear(rg[k]);
+    ring_clear(rg[0]);
+    ring_clear(rg[1]);
+    if constexpr (NR > 2) {
+        ring_clear(rg[2]);
+        ring_clear(rg[3]);
+    }
+    if constexpr (NR > 4) {
+        ring_clear(rg[4]);
+        ring_clear(rg[5]);
+    }
     cx<T> bq[NB];
 #pragma unroll
     for (int k = 0; k < NB; ++k) bq[k] = zero_cx<T>();
@@ -425,8 +437,10 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
         if (PROLONG) x0 = axpy_real((T)0.5, in.e0 + in.e1, x0);
         ring_push<P>(rg[0], dclip<DIR>(clip<MODE>(x0, ln, t, n), L, ln, t));
         bq[P % NB] = in.b;
-#pragma unroll
-        for (int s = 1; s <= S; ++s) {
+// a call per sweep: as an unrolled loop the kernels spill more scalar
+        // registers (FP32 four sweeps 43 instead of 19)
+        auto sweep = [&](auto sc) {
+            constexpr int s = decltype(sc)::value;
             const int r = t - s;
             const Ring<T>& g = rg[s - 1];
             const cx<T> br = bq[qslot<NB>(P, s)];
@@ -434,12 +448,20 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
                 clip<MODE>(cfma(ring_jf<MODE>(ln, r, n), br - ring_apply<P, MODE>(L, g, ln, r), g.v[Q::C]),
                            ln, r, n),
                 L, ln, r);
-            if (s < S) {
+            if constexpr (s < S) {
                 ring_push<P>(rg[s], v);
             } else {
-                if (own & (r >= y0) & (r < y1)) xo[(long long)r * np + ln.i] = UPDATE ? in.u + v : v;
+                if ((r >= y0) & (r < y1)) {
+                    if (own) xo[(long long)r * np + ln.i] = UPDATE ? in.u + v : v;
+                }
                 if constexpr (RESID) ring_push<P>(rg[S], v);
             }
+        };
+        sweep(Int<1>{});
+        sweep(Int<2>{});
+        if constexpr (S == 4) {
+            sweep(Int<3>{});
+            sweep(Int<4>{});
         }
         if constexpr (RESID) {
             // residual of the final iterate, row t - S - 1
@@ -457,8 +479,6 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
     };
 
     SweepIn<T, PROLONG, UPDATE> buf[NBUF];
-#pragma unroll
-    for (int k = 0; k < NBUF - 1; ++k) load(buf[k], tb + k);
     // blocks of CHUNK steps in mode MODE; the blocks whose stencil rows,
     // t - DEPTH .. t + CHUNK - 1, reach row 0 or row n run with the row mode
     // added, in loops of their own before and after the main loop
@@ -479,6 +499,10 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
                 block(Int<5>{});
             }
         };
+        // (loaded here, in each mode's own code: before the branch between the
+        // modes the rows were live across it)
+#pragma unroll
+        for (int k = 0; k < NBUF - 1; ++k) load(buf[k], tb + k);
         int t = tb;
         for (; t <= te && t - DEPTH <= 0; t += CHUNK) chunk(Int<MODE | TOUCH_ROW>{}, t);
         for (; t <= te && t + CHUNK - 1 < n; t += CHUNK) chunk(Int<MODE>{}, t);
@@ -566,7 +590,9 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
             bnew = in.s;
         }
         bnew = dclip<DIR>(bnew, L, ln, rb);
-        if (HSS != 0 && (own & (rb >= y0) & (rb < y1))) rho[(long long)rb * np + ln.i] = bnew;
+        if (HSS != 0 && (rb >= y0) & (rb < y1)) {
+            if (own) rho[(long long)rb * np + ln.i] = bnew;
+        }
         bq[P % 3] = bnew;
         // first sweep (pointwise): row rb
         ring_push<P>(g1, clip<MODE>(ring_jf<MODE>(ln, rb, n) * bnew, ln, rb, n));
@@ -577,7 +603,9 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
                 cfma(ring_jf<MODE>(ln, r, n), bq[qslot<3>(P, 1)] - ring_apply<P, MODE>(L, g1, ln, r),
                      g1.v[Q::C]),
                 L, ln, r);
-            if (own & (r >= y0) & (r < y1)) x[(long long)r * np + ln.i] = v;
+            if ((r >= y0) & (r < y1)) {
+                if (own) x[(long long)r * np + ln.i] = v;
+            }
             ring_push<P>(g2, clip<MODE>(v, ln, r, n));
         }
         // residual: row rb - 2
@@ -599,8 +627,6 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
     constexpr int NBUF = 3;                  // input rows in flight
     constexpr int CHUNK = HSS == 1 ? 6 : 3;  // a multiple of 3, NBUF and the R queue's 2
     PreIn<T> buf[NBUF];
-#pragma unroll
-    for (int k = 0; k < NBUF - 1; ++k) load(buf[k], tb + k);
     // blocks of CHUNK steps in mode MODE; the blocks whose stencil rows,
     // t - DEPTH .. t + CHUNK - 1, reach row 0 or row n run with the row mode
     // added, in loops of their own before and after the main loop
@@ -621,6 +647,10 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
                 block(Int<5>{});
             }
         };
+        // (loaded here, in each mode's own code: before the branch between the
+        // modes the rows were live across it)
+#pragma unroll
+        for (int k = 0; k < NBUF - 1; ++k) load(buf[k], tb + k);
         int t = tb;
         for (; t <= te && t - DEPTH <= 0; t += CHUNK) chunk(Int<MODE | TOUCH_ROW>{}, t);
         for (; t <= te && t + CHUNK - 1 < n; t += CHUNK) chunk(Int<MODE>{}, t);
@@ -639,7 +669,7 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
 
 }  // namespace
 
-StreamGrid stream_grid(int n, int halo, int ns, int H) {
+static StreamGrid stream_grid(int n, int halo, int ns, int H) {
     StreamGrid g;
     g.H = H;
     g.strips = (unsigned)strip_count(n, halo);
@@ -659,7 +689,8 @@ StreamGrid stream_grid(int n, int halo, int ns, int H) {
 // time a configuration (kernel, mesh size, slot count, precision) is launched
 // on a stream that is not being captured, every candidate height is timed
 // on the real operands (all the kernels timed this way recompute the same
-// outputs from unchanged inputs) and the fastest is kept for the process.
+// outputs from unchanged inputs), the best three again, and the fastest is kept
+// for the process.
 // Until then, and under capture, a model picks the height: the larger of one
 // wavefront's chain (about 1.2 us per step) and all wavefronts' steps at the
 // chip's throughput (about 1400 wavefront-steps per microsecond).
@@ -682,7 +713,7 @@ static unsigned stream_blocks(const StreamGrid& g) {
     return g.eblocks + (g.units - g.edge_units + SW - 1) / SW;
 }
 
-enum StreamKind : int { SK_S4R = 0, SK_S2P, SK_S2R, SK_S4P, SK_S1, SK_PRE0, SK_PRE1, SK_PRE2, SK_DIR = 16 };
+enum StreamKind : int { SK_S4R = 0, SK_S2P, SK_PRE0, SK_PRE1, SK_PRE2, SK_DIR = 16 };
 
 struct RowsKey {
     int kind, n, ns, bytes;
@@ -723,22 +754,41 @@ static int stream_rows(hipStream_t st, RowsKey key, int halo, bool tune, F launc
         (void)hipEventDestroy(e0);
         return model;
     }
-    int best = model;
-    float tbest = 1e30f;
-    for (int H : cand) {
-        if (H > key.n + 1 && H != 4) break;
-        launch(H);  // warm
+    auto timed = [&](int H) {  // two launches, ms; negative on an error
+        float ms = -1.f;
         (void)hipEventRecord(e0, st);
         launch(H);
         launch(H);
         (void)hipEventRecord(e1, st);
-        if (hipEventSynchronize(e1) != hipSuccess) break;
-        float ms = 0.f;
-        if (hipEventElapsedTime(&ms, e0, e1) == hipSuccess && ms < tbest) {
-            tbest = ms;
-            best = H;
-        }
+        if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess) return -1.f;
+        return ms;
+    };
+    // from the tallest down; the time falls with the chain and rises again with
+    // the halo, so two heights in a row well above the best end the search
+    std::vector<std::pair<float, int>> seen;
+    float tbest = 1e30f;
+    int above = 0;
+    launch(cand[std::size(cand) - 1]);  // warm
+    for (int q = (int)std::size(cand) - 1; q >= 0 && above < 2; --q) {
+        const int H = cand[q];
+        if (H > key.n + 1 && H != 4) continue;
+        const float ms = timed(H);
+        if (ms < 0.f) break;
+        seen.emplace_back(ms, H);
+        tbest = std::min(tbest, ms);
+        above = ms > 1.4f * tbest ? above + 1 : 0;
     }
+    // the three best again, in turn: one timing of two launches varies by more
+    // than they differ (FP64 four-sweep at 4 x 1024^2: 66 us at H = 42, and a
+    // residual pass of 61 us at H = 42 was run at H = 16, 68 us)
+    std::sort(seen.begin(), seen.end());
+    if (seen.size() > 3) seen.resize(3);
+    for (int r = 0; r < 3 && seen.size() > 1; ++r)
+        for (auto& c : seen) {
+            const float ms = timed(c.second);
+            if (ms >= 0.f) c.first = r == 0 ? ms : std::min(c.first, ms);
+        }
+    const int best = seen.empty() ? model : std::min_element(seen.begin(), seen.end())->second;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     std::lock_guard<std::mutex> lk(g_rows_mu);
@@ -757,9 +807,6 @@ bool stream_sweeps_2d(hipStream_t st, const Op2<T>& L, int S, Vec<const cx<T>> X
     int kind = -1;
     if (S == 4 && pro && resid && !update) kind = SK_S4R;
     else if (S == 2 && pro && !resid) kind = SK_S2P;  // the update variant shares its height
-    else if (S == 2 && !pro && resid && !update) kind = SK_S2R;
-    else if (S == 4 && pro && !resid && !update) kind = SK_S4P;
-    else if (S == 1 && !pro && !resid && !update) kind = SK_S1;
     if (kind < 0) return false;
     const bool dir = L.dir != 0u;
     auto launch = [&](int H) {
@@ -771,11 +818,8 @@ bool stream_sweeps_2d(hipStream_t st, const Op2<T>& L, int S, Vec<const cx<T>> X
         else k_stream_sweeps<T, SS, PP, RR, UU, false><<<nb, WAVE * SW, 0, st>>>(L, Xin, Ec, B, Xout, Bc, g); \
     } while (0)
         if (kind == SK_S4R) HELM_STREAM(4, true, true, false);
-        else if (kind == SK_S2P && update) HELM_STREAM(2, true, false, true);
-        else if (kind == SK_S2P) HELM_STREAM(2, true, false, false);
-        else if (kind == SK_S2R) HELM_STREAM(2, false, true, false);
-        else if (kind == SK_S4P) HELM_STREAM(4, true, false, false);
-        else HELM_STREAM(1, false, false, false);
+        else if (update) HELM_STREAM(2, true, false, true);
+        else HELM_STREAM(2, true, false, false);
 #undef HELM_STREAM
     };
     // u += x is not safe to repeat: the update launch only looks up
