@@ -4,14 +4,10 @@
 #pragma once
 
 // y = D^{-1} (b - L x) (MODE_PRES; X null means x = 0) or y = D^{-1} L x
-// (MODE_PAPPLY) on level l in FP64: the Jacobi factors with omega = 1.
+// (MODE_PAPPLY) on 3D level l in FP64: the Jacobi factors with omega = 1.
 void pmode(helm_t* h, int l, int mode, Vec<const cxd> X, Vec<const cxd> B, Vec<cxd> Y, int ns) {
-    const Coef cf = h->coef(HELM_OP_L);
-    if (h->dim == 2)
-        stencil2d<double, double>(h->stream, make_op2<double>(cf, h->nl[l], 1.0), mode, 1.0, X, B, Y, ns);
-    else
-        stencil3d<double, double>(h->stream, make_op3<double>(cf, h->nl[l], 1.0), mode, 1.0, X, B, Y, ns,
-                                  false);
+    stencil3d<double, double>(h->stream, make_op3<double>(h->coef(HELM_OP_L), h->nl[l], 1.0), mode, 1.0, X, B, Y,
+                              ns, false);
 }
 
 // m = smooth_its iterations of Jacobi-left-preconditioned GMRES for
