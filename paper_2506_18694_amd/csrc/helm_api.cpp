@@ -701,7 +701,8 @@ Vec<cx<T>> vcycle2d_zero(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const
 // level 1 without a partner (pair_levels): while the launches are small its
 // post-smoothing shares the finest level's, with the next b1 in the buffer that
 // its result would have taken (the two swap).  marks: time the finest level's
-// launch; returns the complex values per node that it moves.
+// launch, which then stays a launch of its own (the same bits); returns the
+// complex values per node that it moves.
 template <typename T>
 double cycle_rest2d(helm_t* h, const Layout& Lw, void* ws, const Op2<T>& L, int S, Vec<const cx<T>> x,
                     Vec<const cx<T>> rho, Vec<cx<T>> out, bool update, Vec<cx<T>>& b1, Vec<cx<T>> x1,
@@ -717,14 +718,11 @@ double cycle_rest2d(helm_t* h, const Layout& Lw, void* ws, const Op2<T>& L, int 
         stream_pre_2d<T>(h->stream, L1, L1, (T)0, none, none, nil, cst(b1), x1, b2, ns);
         const Vec<const cx<T>> ecc = cst(vcycle2d_zero<T>(h, Lw, ws, 2, cst(b2), at_ws<cx<T>>(ws, Lw.mg_x[2], N2),
                                                           at_ws<cx<T>>(ws, Lw.mg_t[2], N2), ns));
-        if (marks) h->prof_mark();
-        if (tile_post_pair_2d<T>(h->stream, L, L1, S, x, rho, cst(x1), cst(b1), ecc, out, S == 4 ? t1 : nil,
-                                 update, ns)) {
-            if (marks) h->prof_mark();
+        if (!marks && tile_post_pair_2d<T>(h->stream, L, L1, S, x, rho, cst(x1), cst(b1), ecc, out,
+                                           S == 4 ? t1 : nil, update, ns)) {
             if (S == 4) std::swap(b1, t1);
-            return passes + 0.3125;
+            return passes;
         }
-        if (marks && h->prof_used > 0) --h->prof_used;
         STREAMCHK(stream_sweeps_2d<T>(h->stream, L1, 2, cst(x1), ecc, cst(b1), t1, nil, false, ns));
         ec = cst(t1);
     } else {
