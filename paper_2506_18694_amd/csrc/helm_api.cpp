@@ -419,7 +419,8 @@ Layout layout(const helm_t* h, int nrhs) {
         L.ghu2 = take(sizeof(cxd) * (size_t)nrhs * (m + 1));
         L.gn = take(sizeof(double) * (size_t)nrhs * (m + 1));
         L.gy = take(sizeof(cxd) * (size_t)nrhs * m);
-        const int gblk = std::max(nblk, (int)((N + GMRES_BLOCK - 1) / GMRES_BLOCK));
+        int gblk = nblk;  // a coarser level can have more workgroups than a finer one
+        for (int l = 0; l < h->levels; ++l) gblk = std::max(gblk, gmres_blocks(h->Nl[l]));
         L.gpart = take(sizeof(cxd) * (size_t)nrhs * (m + 1) * gblk);
         L.gpart2 = take(sizeof(cxd) * (size_t)nrhs * (m + 1) * gblk);
         L.gnpart = take(sizeof(double) * (size_t)nrhs * gblk);

@@ -12,14 +12,22 @@
 // Larger levels take 3 m + 2 launches (k_gmres_start, per iteration
 // k_gmres_apply and two k_gmres_orth, k_gmres_finish): every inner product is
 // left as one partial sum per workgroup, which the next launch's workgroups
-// add up themselves, so that a reduction costs no launch of its own.  Both
+// add up themselves, so that a reduction costs no launch of its own.  That is
+// as many reads as the square of the workgroups, so a column has GMRES_MOST
+// workgroups at most, which then take several chunks of nodes each (MANY): with
+// one chunk each a smoothing took 3.20 ms at 2048^2 and 38.3 at 4096^2, where
+// 56 launches took 1.60 and 6.76; now 1.11 and 5.14 (with at most 256 workgroups
+// 1.28 and 7.45, with 512 1.11 and 4.97, with 1024 1.14 and 5.16).  The count
+// follows from the nodes alone: a
+// column's sums do not depend on how many columns share the launch.  Both
 // keep the Krylov vectors unnormalised, w_0 = r and w_{j+1} the vector before
 // its division by h_{j+1,j}, with their norms beside them: V_i = w_i / |w_i|
 // enters through its scale, and no pass normalises.
 // Measured per smoothing (m = 5, one column): about 190 us as 56 launches; 19 us
 // in one workgroup at 576 nodes, 33 at 2209, and 75 us as 17 launches at 8649
-// to 34225.  The one-workgroup form is a chain of 16 inner products; summed
-// over the wavefront with LDS shuffles they took 34 and 48 us of it.
+// to 34225, 115 at 512^2 (270 as 56).  The one-workgroup form is a chain of 16
+// inner products; summed over the wavefront with LDS shuffles they took 34 and
+// 48 us of it.
 #include "launch.h"
 
 namespace helm {
@@ -358,23 +366,38 @@ __device__ __forceinline__ cxd apply_mem(const Op2<double>& L, const Row& r, con
     return cfma(L.wDg, ne + sw, cfma(r.x, e + w, cfma(r.y, nn + ss, r.c * c)));
 }
 
-// partial sums of conj(w_i) w over this workgroup's nodes, i < cnt:
-// part[i nblk + blk]
-__device__ __forceinline__ void dots(const cxd* G, long long N, int cnt, const cxd (&w)[NPB], const long long (&t)[NPB],
-                                     cxd* part, int nblk, int blk, double* lds) {
+// this thread's nodes of chunk r of the workgroup
+__device__ __forceinline__ long long node_at(int chunks, int blk, int r, int u) {
+    return (((long long)blk * chunks + r) * NPB + u) * BS + threadIdx.x;
+}
+
+// partial sums of conj(w_i) w over this workgroup's nodes, i < cnt, w the
+// vector cnt: part[i nblk + blk]; wl: w on the last chunk
+__device__ __forceinline__ void dots(const cxd* G, long long N, int cnt, const cxd (&wl)[NPB], cxd* part,
+                                     int nblk, int chunks, int blk, double* lds) {
     for (int i0 = 0; i0 < cnt; i0 += GROUP) {
         double d[2 * GROUP];
 #pragma unroll
         for (int k = 0; k < 2 * GROUP; ++k) d[k] = 0.0;
-#pragma unroll
-        for (int k = 0; k < GROUP; ++k) {
-            if (i0 + k >= cnt) continue;
-            const cxd* v = G + (long long)(i0 + k) * N;
+        for (int r = 0; r < chunks; ++r) {
+            long long t[NPB];
+            cxd w[NPB];
 #pragma unroll
             for (int u = 0; u < NPB; ++u) {
-                const cxd a = cjmul(v[t[u] < N ? t[u] : 0], w[u]);  // w is zero past the end
-                d[2 * k] += a.x;
-                d[2 * k + 1] += a.y;
+                t[u] = node_at(chunks, blk, r, u);
+                w[u] = wl[u];
+                if (r + 1 < chunks) w[u] = t[u] < N ? G[(long long)cnt * N + t[u]] : zero_c();
+            }
+#pragma unroll
+            for (int k = 0; k < GROUP; ++k) {
+                if (i0 + k >= cnt) continue;
+                const cxd* v = G + (long long)(i0 + k) * N;
+#pragma unroll
+                for (int u = 0; u < NPB; ++u) {
+                    const cxd a = cjmul(v[t[u] < N ? t[u] : 0], w[u]);  // w is zero past the end
+                    d[2 * k] += a.x;
+                    d[2 * k + 1] += a.y;
+                }
             }
         }
         block_sum0<2 * GROUP>(d, lds);
@@ -387,26 +410,29 @@ __device__ __forceinline__ void dots(const cxd* G, long long N, int cnt, const c
 }
 
 // w_0 = D^{-1}(b - L x) (x = 0 without a guess) and its partial sums of squares
+template <bool MANY>
 __global__ __launch_bounds__(BS) void k_gmres_start(Op2<double> L, Vec<const cxd> Bv, Vec<const cxd> Xv, int guess,
                                                     GmresWs g) {
     __shared__ double lds[(BS / WAVE) * 16];
-    const int slot = blockIdx.x / g.nblk, blk = blockIdx.x % g.nblk;
+    const int slot = blockIdx.x / g.nblk, blk = blockIdx.x % g.nblk, chunks = MANY ? g.chunks : 1;
     const int W = L.n + 1;
     const long long N = (long long)W * W;
     const cxd *b = Bv.at(slot), *x = Xv.at(slot);
     cxd* G = g.basis + slot * g.bstride;
     double s[1] = {0.0};
+    for (int r = 0; r < chunks; ++r) {
 #pragma unroll
-    for (int u = 0; u < NPB; ++u) {
-        const long long t = ((long long)blk * NPB + u) * BS + threadIdx.x;
-        if (t >= N) continue;
-        const int j = (int)(t / W), i = (int)(t - (long long)j * W);
-        const Row r = row_of(L, i, j);
-        cxd v = b[t];
-        if (guess) v = v - apply_mem(L, r, x, i, j);
-        v = r.jf * v;
-        G[t] = v;
-        s[0] += v.x * v.x + v.y * v.y;
+        for (int u = 0; u < NPB; ++u) {
+            const long long t = node_at(chunks, blk, r, u);
+            if (t >= N) continue;
+            const int j = (int)(t / W), i = (int)(t - (long long)j * W);
+            const Row row = row_of(L, i, j);
+            cxd v = b[t];
+            if (guess) v = v - apply_mem(L, row, x, i, j);
+            v = row.jf * v;
+            G[t] = v;
+            s[0] += v.x * v.x + v.y * v.y;
+        }
     }
     block_sum0<1>(s, lds);
     if (threadIdx.x == 0) g.npart[(long long)slot * g.nblk + blk] = s[0];
@@ -414,52 +440,57 @@ __global__ __launch_bounds__(BS) void k_gmres_start(Op2<double> L, Vec<const cxd
 
 // w_{j+1} = D^{-1} L w_j / |w_j|, the partial inner products with w_0 .. w_j;
 // |w_j| is added up from its partial sums
+template <bool MANY>
 __global__ __launch_bounds__(BS) void k_gmres_apply(Op2<double> L, int j, GmresWs g) {
     __shared__ double lds[(BS / WAVE) * 16];
-    const int slot = blockIdx.x / g.nblk, blk = blockIdx.x % g.nblk;
+    const int slot = blockIdx.x / g.nblk, blk = blockIdx.x % g.nblk, chunks = MANY ? g.chunks : 1;
     const int W = L.n + 1;
     const long long N = (long long)W * W;
     cxd* G = g.basis + slot * g.bstride;
     const double nrm = norm_from(g.npart + (long long)slot * g.nblk, g.nblk, lds), sc = inv_norm(nrm);
     if (blk == 0 && threadIdx.x == 0) g.norms[slot * (g.m + 1) + j] = nrm;
     cxd w[NPB];
-    long long t[NPB];
+    for (int r = 0; r < chunks; ++r) {
 #pragma unroll
-    for (int u = 0; u < NPB; ++u) {
-        t[u] = ((long long)blk * NPB + u) * BS + threadIdx.x;
-        w[u] = zero_c();
-        if (t[u] >= N) continue;
-        const int jj = (int)(t[u] / W), i = (int)(t[u] - (long long)jj * W);
-        const Row r = row_of(L, i, jj);
-        w[u] = sc * (r.jf * apply_mem(L, r, G + (long long)j * N, i, jj));
-        G[(long long)(j + 1) * N + t[u]] = w[u];
+        for (int u = 0; u < NPB; ++u) {
+            const long long t = node_at(chunks, blk, r, u);
+            w[u] = zero_c();
+            if (t >= N) continue;
+            const int jj = (int)(t / W), i = (int)(t - (long long)jj * W);
+            const Row row = row_of(L, i, jj);
+            w[u] = sc * (row.jf * apply_mem(L, row, G + (long long)j * N, i, jj));
+            G[(long long)(j + 1) * N + t] = w[u];
+        }
     }
-    dots(G, N, j + 1, w, t, g.part[0] + (long long)slot * (g.m + 1) * g.nblk, g.nblk, blk, lds);
+    dots(G, N, j + 1, w, g.part[0] + (long long)slot * (g.m + 1) * g.nblk, g.nblk, chunks, blk, lds);
 }
 
 // One Gram-Schmidt pass on w_{j+1}: the coefficients from the partial inner
 // products, w -= sum V_i h_i; the first pass leaves the inner products of the
 // second, the second the partial sums of squares.  C: j + 1, whose vectors are
-// then requested before the coefficients are added up and used from registers;
-// 0: any count.
-template <int C>
+// then used from registers, those of the first chunk requested before the
+// coefficients are added up; 0: any count.
+template <int C, bool MANY>
 __global__ __launch_bounds__(BS) void k_gmres_orth(long long N, int j, int pass, GmresWs g) {
     __shared__ double lds[(BS / WAVE) * 16];
     __shared__ cxd c[GMRES_MAX_ITS];
-    const int slot = blockIdx.x / g.nblk, blk = blockIdx.x % g.nblk;
+    const int slot = blockIdx.x / g.nblk, blk = blockIdx.x % g.nblk, chunks = MANY ? g.chunks : 1;
     cxd* G = g.basis + slot * g.bstride;
     const cxd* part = g.part[pass] + (long long)slot * (g.m + 1) * g.nblk;
     const int lane = (int)threadIdx.x % WAVE, wv = (int)threadIdx.x / WAVE;
     cxd w[NPB], v[C > 0 ? C : 1][NPB];
     long long t[NPB];
+    auto load = [&](int r) {
 #pragma unroll
-    for (int u = 0; u < NPB; ++u) {
-        t[u] = ((long long)blk * NPB + u) * BS + threadIdx.x;
-        const long long p = t[u] < N ? t[u] : 0;
-        w[u] = G[(long long)(j + 1) * N + p];
+        for (int u = 0; u < NPB; ++u) {
+            t[u] = node_at(chunks, blk, r, u);
+            const long long p = t[u] < N ? t[u] : 0;
+            w[u] = G[(long long)(j + 1) * N + p];
 #pragma unroll
-        for (int i = 0; i < C; ++i) v[i][u] = G[(long long)i * N + p];
-    }
+            for (int i = 0; i < C; ++i) v[i][u] = G[(long long)i * N + p];
+        }
+    };
+    load(0);
     for (int i = wv; i <= j; i += BS / WAVE) {  // a wavefront per coefficient
         double d[2] = {0.0, 0.0};
         for (int q = lane; q < g.nblk; q += WAVE) {
@@ -479,21 +510,36 @@ __global__ __launch_bounds__(BS) void k_gmres_orth(long long N, int j, int pass,
         }
     }
     __syncthreads();
-    double s[1] = {0.0};
+    double s[1] = {0.0}, d[C > 0 ? 2 * C : 1] = {};
+    for (int r = 0; r < chunks; ++r) {
+        if (r > 0) load(r);
 #pragma unroll
-    for (int u = 0; u < NPB; ++u) {
-        if (t[u] >= N) {
-            w[u] = zero_c();
-            continue;
+        for (int u = 0; u < NPB; ++u) {
+            if (t[u] >= N) {
+                w[u] = zero_c();
+                continue;
+            }
+            if constexpr (C > 0) {
+#pragma unroll
+                for (int i = 0; i < C; ++i) w[u] = w[u] - c[i] * v[i][u];
+            } else {
+                for (int i = 0; i <= j; ++i) w[u] = w[u] - c[i] * G[(long long)i * N + t[u]];
+            }
+            G[(long long)(j + 1) * N + t[u]] = w[u];
+            s[0] += w[u].x * w[u].x + w[u].y * w[u].y;
         }
         if constexpr (C > 0) {
+            if (pass == 0) {
 #pragma unroll
-            for (int i = 0; i < C; ++i) w[u] = w[u] - c[i] * v[i][u];
-        } else {
-            for (int i = 0; i <= j; ++i) w[u] = w[u] - c[i] * G[(long long)i * N + t[u]];
+                for (int i = 0; i < C; ++i) {
+                    cxd a = mk(d[2 * i], d[2 * i + 1]);
+#pragma unroll
+                    for (int u = 0; u < NPB; ++u) a = a + cjmul(v[i][u], w[u]);
+                    d[2 * i] = a.x;
+                    d[2 * i + 1] = a.y;
+                }
+            }
         }
-        G[(long long)(j + 1) * N + t[u]] = w[u];
-        s[0] += w[u].x * w[u].x + w[u].y * w[u].y;
     }
     if (pass == 1) {
         block_sum0<1>(s, lds);
@@ -502,33 +548,25 @@ __global__ __launch_bounds__(BS) void k_gmres_orth(long long N, int j, int pass,
     }
     cxd* out = g.part[1] + (long long)slot * (g.m + 1) * g.nblk;
     if constexpr (C > 0) {
-        double d[2 * C];
-#pragma unroll
-        for (int i = 0; i < C; ++i) {
-            cxd a = zero_c();
-#pragma unroll
-            for (int u = 0; u < NPB; ++u) a = a + cjmul(v[i][u], w[u]);
-            d[2 * i] = a.x;
-            d[2 * i + 1] = a.y;
-        }
         block_sum0<2 * C>(d, lds);
         if (threadIdx.x == 0) {
 #pragma unroll
             for (int i = 0; i < C; ++i) out[(long long)i * g.nblk + blk] = mk(d[2 * i], d[2 * i + 1]);
         }
     } else {
-        dots(G, N, j + 1, w, t, out, g.nblk, blk, lds);
+        dots(G, N, j + 1, w, out, g.nblk, chunks, blk, lds);
     }
 }
 
 // The least-squares problem (every workgroup solves it for itself) and
 // x (+)= V y.
+template <bool MANY>
 __global__ __launch_bounds__(BS) void k_gmres_finish(long long N, int guess, Vec<cxd> Xv, GmresWs g) {
     __shared__ double lds[(BS / WAVE) * 16];
     __shared__ cxd H[GMRES_MAX_ITS * (GMRES_MAX_ITS + 1)], gv[GMRES_MAX_ITS + 1], cs[GMRES_MAX_ITS], sn[GMRES_MAX_ITS];
     __shared__ cxd y[GMRES_MAX_ITS];
     __shared__ double nr[GMRES_MAX_ITS + 1];
-    const int slot = blockIdx.x / g.nblk, blk = blockIdx.x % g.nblk, m = g.m;
+    const int slot = blockIdx.x / g.nblk, blk = blockIdx.x % g.nblk, m = g.m, chunks = MANY ? g.chunks : 1;
     const double last = norm_from(g.npart + (long long)slot * g.nblk, g.nblk, lds);
     for (int q = threadIdx.x; q < m * (m + 1); q += BS) H[q] = g.hess[(long long)slot * m * (m + 1) + q];
     for (int q = threadIdx.x; q <= m; q += BS) nr[q] = q < m ? g.norms[slot * (m + 1) + q] : last;
@@ -563,46 +601,56 @@ __global__ __launch_bounds__(BS) void k_gmres_finish(long long N, int guess, Vec
     __syncthreads();
     const cxd* G = g.basis + slot * g.bstride;
     cxd* x = Xv.at(slot);
+    for (int r = 0; r < chunks; ++r) {
 #pragma unroll
-    for (int u = 0; u < NPB; ++u) {
-        const long long t = ((long long)blk * NPB + u) * BS + threadIdx.x;
-        if (t >= N) continue;
-        cxd v = guess ? x[t] : zero_c();
-        for (int i = 0; i < m; ++i) v = cfma(y[i], G[(long long)i * N + t], v);
-        x[t] = v;
+        for (int u = 0; u < NPB; ++u) {
+            const long long t = node_at(chunks, blk, r, u);
+            if (t >= N) continue;
+            cxd v = guess ? x[t] : zero_c();
+            for (int i = 0; i < m; ++i) v = cfma(y[i], G[(long long)i * N + t], v);
+            x[t] = v;
+        }
     }
 }
 
 }  // namespace
 
 bool gmres_one_2d(hipStream_t st, const Op2<double>& L, int m, Vec<const cxd> B, Vec<cxd> X, bool guess, int ns) {
-    const int N = (L.n + 1) * (L.n + 1), S = L.n + 3;
-    if (L.n > 63 || N > 5 * OT || m > GMRES_ONE_ITS) return false;
+    const long long N = (long long)(L.n + 1) * (L.n + 1);
+    const int S = L.n + 3;
+    if (N > 5 * OT || m > GMRES_ONE_ITS) return false;
     const size_t lds = sizeof(cxd) * (size_t)S * S;
     if (N <= 2 * OT) k_gmres_one<2><<<ns, OT, lds, st>>>(L, m, B, X, guess ? 1 : 0);
     else k_gmres_one<5><<<ns, OT, lds, st>>>(L, m, B, X, guess ? 1 : 0);
     return true;
 }
 
-void gmres_2d(hipStream_t st, const Op2<double>& L, Vec<const cxd> B, Vec<cxd> X, bool guess, const GmresWs& g, int ns) {
+template <bool MANY>
+static void gmres_launch(hipStream_t st, const Op2<double>& L, Vec<const cxd> B, Vec<cxd> X, bool guess, const GmresWs& g,
+                         int ns) {
     const long long N = (long long)(L.n + 1) * (L.n + 1);
     const unsigned nb = (unsigned)(g.nblk * ns);
     const int gs = guess ? 1 : 0;
-    k_gmres_start<<<nb, BS, 0, st>>>(L, B, Vec<const cxd>{X.base, X.cstride, X.off, X.cols}, gs, g);
+    k_gmres_start<MANY><<<nb, BS, 0, st>>>(L, B, Vec<const cxd>{X.base, X.cstride, X.off, X.cols}, gs, g);
     for (int j = 0; j < g.m; ++j) {
-        k_gmres_apply<<<nb, BS, 0, st>>>(L, j, g);
+        k_gmres_apply<MANY><<<nb, BS, 0, st>>>(L, j, g);
         for (int pass = 0; pass < 2; ++pass) {
             switch (j) {
-                case 0: k_gmres_orth<1><<<nb, BS, 0, st>>>(N, j, pass, g); break;
-                case 1: k_gmres_orth<2><<<nb, BS, 0, st>>>(N, j, pass, g); break;
-                case 2: k_gmres_orth<3><<<nb, BS, 0, st>>>(N, j, pass, g); break;
-                case 3: k_gmres_orth<4><<<nb, BS, 0, st>>>(N, j, pass, g); break;
-                case 4: k_gmres_orth<5><<<nb, BS, 0, st>>>(N, j, pass, g); break;
-                default: k_gmres_orth<0><<<nb, BS, 0, st>>>(N, j, pass, g);
+                case 0: k_gmres_orth<1, MANY><<<nb, BS, 0, st>>>(N, j, pass, g); break;
+                case 1: k_gmres_orth<2, MANY><<<nb, BS, 0, st>>>(N, j, pass, g); break;
+                case 2: k_gmres_orth<3, MANY><<<nb, BS, 0, st>>>(N, j, pass, g); break;
+                case 3: k_gmres_orth<4, MANY><<<nb, BS, 0, st>>>(N, j, pass, g); break;
+                case 4: k_gmres_orth<5, MANY><<<nb, BS, 0, st>>>(N, j, pass, g); break;
+                default: k_gmres_orth<0, MANY><<<nb, BS, 0, st>>>(N, j, pass, g);
             }
         }
     }
-    k_gmres_finish<<<nb, BS, 0, st>>>(N, gs, X, g);
+    k_gmres_finish<MANY><<<nb, BS, 0, st>>>(N, gs, X, g);
+}
+
+void gmres_2d(hipStream_t st, const Op2<double>& L, Vec<const cxd> B, Vec<cxd> X, bool guess, const GmresWs& g, int ns) {
+    if (g.chunks > 1) gmres_launch<true>(st, L, B, X, guess, g, ns);
+    else gmres_launch<false>(st, L, B, X, guess, g, ns);
 }
 
 }  // namespace helm

@@ -137,14 +137,23 @@ void vcycle_small(hipStream_t st, const SmallCycle<T>& sc, size_t lds_bytes, con
 // (guess) or from 0; L carries the Jacobi factors of omega = 1.
 constexpr int GMRES_ONE_ITS = 5;    // most iterations of the one-workgroup form
 constexpr int GMRES_MAX_ITS = 20;   // most iterations
-constexpr int GMRES_BLOCK = 512;    // nodes per workgroup of the other one
+constexpr int GMRES_BLOCK = 512;    // nodes per chunk of the other one
+constexpr int GMRES_MOST = 768;     // most workgroups per column of the other one
+// chunks per workgroup and workgroups per column
+inline int gmres_chunks(long long N) {
+    return (int)((N + (long long)GMRES_BLOCK * GMRES_MOST - 1) / ((long long)GMRES_BLOCK * GMRES_MOST));
+}
+inline int gmres_blocks(long long N) {
+    const long long nodes = (long long)GMRES_BLOCK * gmres_chunks(N);
+    return (int)((N + nodes - 1) / nodes);
+}
 // in one workgroup per column; false (and nothing launched) for more than
 // 2560 nodes or more than GMRES_ONE_ITS iterations
 bool gmres_one_2d(hipStream_t st, const Op2<double>& L, int m, Vec<const cxd> B, Vec<cxd> X, bool guess, int ns);
 // in 3 m + 2 launches.  Per slot: m + 1 Krylov vectors (basis, bstride apart),
 // m columns of m + 1 Hessenberg entries, m + 1 norms, and per workgroup (nblk
-// = nodes / GMRES_BLOCK, rounded up) m + 1 partial sums in each of part[0],
-// part[1] and one in npart.
+// = gmres_blocks) m + 1 partial sums in each of part[0], part[1] and one in
+// npart.
 struct GmresWs {
     cxd* basis;
     long long bstride;
@@ -152,7 +161,7 @@ struct GmresWs {
     double* norms;
     cxd* part[2];
     double* npart;
-    int m, nblk;
+    int m, nblk, chunks;  // chunks = gmres_chunks
 };
 void gmres_2d(hipStream_t st, const Op2<double>& L, Vec<const cxd> B, Vec<cxd> X, bool guess, const GmresWs& g, int ns);
 

@@ -36,7 +36,7 @@ void gmres_smooth(helm_t* h, const Layout& Lw, void* ws, int l, Vec<const cxd> b
         const Op2<double> L = make_op2<double>(h->coef(HELM_OP_L), h->nl[l], 1.0);
         if (gmres_one_2d(st, L, m, b, x, guess, ns)) return;
         const GmresWs g{G, cs, hu, hn, {part, reinterpret_cast<cxd*>(w + Lw.gpart2)}, npart, m,
-                        (int)((N + GMRES_BLOCK - 1) / GMRES_BLOCK)};
+                        gmres_blocks(N), gmres_chunks(N)};
         gmres_2d(st, L, b, x, guess, g, ns);
         return;
     }
