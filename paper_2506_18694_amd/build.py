@@ -19,7 +19,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libhelm.so")
 BUILD = os.path.join(HERE, "_build")
 
-SOURCES = ["kernels2d.hip", "kernels2d_fused.hip", "kernels2d_stream.hip", "kernels2d_tile.hip", "kernels2d_small.hip", "kernels2d_gmres.hip", "kernels3d.hip", "kernels3d_fused.hip", "kernels3d_block.hip", "kernels2d_mixed.hip", "kernels_vec.hip", "helm_api.cpp"]
+SOURCES = ["kernels2d.hip", "kernels2d_fused.hip", "kernels2d_stream.hip", "kernels2d_tile.hip", "kernels2d_small.hip", "kernels2d_gmres.hip", "kernels3d.hip", "kernels3d_fused.hip", "kernels3d_columns.hip", "kernels3d_block.hip", "kernels2d_mixed.hip", "kernels_vec.hip", "helm_api.cpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
@@ -48,7 +48,7 @@ def _compile(src):
 def build(verbose=False):
     """Compile every HIP source and link libhelm.so.  Always rebuilds."""
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(6, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp"
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs

@@ -814,14 +814,22 @@ void hss_step_generic(helm_t* h, const Layout& Lw, void* ws, int ns, int s) {
     axpy1<T>(h->stream, N, (T)1, cst(e), u, ns);
 }
 
+// One pass of a 3D step on a level of any size: on blocks of the mesh where
+// the launch is small, else marching, below BLOCK3D_N with the blocks' roundings.
+template <typename T>
+void step3d(hipStream_t st, const Op3F<T>& L, int first, int nj, bool pro, int upd, T s, Vec<const cx<T>> X,
+            Vec<const cx<T>> B, Vec<const cx<T>> Ec, Vec<cx<T>> Rho, Vec<cx<T>> Y, Vec<cx<T>> Bc, int ns) {
+    if (block3d<T>(st, L, L, first, nj, pro, upd, s, X, B, Ec, Rho, Y, Bc, ns)) return;
+    if (L.n < BLOCK3D_N) STREAMCHK(columns3d<T>(st, L, first, nj, pro, upd, s, X, B, Ec, Rho, Y, Bc, ns));
+    else STREAMCHK((pass3d<T, T>(st, L, first, nj, pro, upd, s, X, B, Ec, Rho, Y, Bc, ns)));
+}
+
 // The zero-guess pre-smoothing x of L x = b on a 3D level and the restriction
 // b_c of its residual, in one pass.
 template <typename T>
 void pre3d(helm_t* h, const Op3F<T>& L, Vec<const cx<T>> b, Vec<cx<T>> x, Vec<cx<T>> bc, int ns) {
     const Vec<const cx<T>> none{};
-    const Vec<cx<T>> nil{};
-    if (block3d<T>(h->stream, L, L, F_JAC0, 1, false, 0, (T)1, none, b, none, nil, x, bc, ns)) return;
-    STREAMCHK((pass3d<T, T>(h->stream, L, F_JAC0, 1, false, 0, (T)1, none, b, none, nil, x, bc, ns)));
+    step3d<T>(h->stream, L, F_JAC0, 1, false, 0, (T)1, none, b, none, Vec<cx<T>>{}, x, bc, ns);
 }
 
 // Prolongation of ec, correction of x and both post-smoothing sweeps, in one
@@ -830,9 +838,7 @@ template <typename T>
 void post3d(helm_t* h, const Op3F<T>& L, Vec<const cx<T>> x, Vec<const cx<T>> b, Vec<const cx<T>> ec, Vec<cx<T>> y,
             bool add, int ns) {
     const Vec<cx<T>> nil{};
-    const int upd = add ? 1 : 0;
-    if (block3d<T>(h->stream, L, L, F_JAC, 2, true, upd, (T)1, x, b, ec, nil, y, nil, ns)) return;
-    STREAMCHK((pass3d<T, T>(h->stream, L, F_JAC, 2, true, upd, (T)1, x, b, ec, nil, y, nil, ns)));
+    step3d<T>(h->stream, L, F_JAC, 2, true, add ? 1 : 0, (T)1, x, b, ec, nil, y, nil, ns);
 }
 
 // Fused 3D cycle from a zero initial guess on level l, two passes per level
@@ -884,26 +890,22 @@ void hss_step3d_fused(helm_t* h, const Layout& Lw, void* ws, int ns, int s) {
     const Vec<const cx<T>> none{};
     const Vec<cx<T>> nil{};
     hipStream_t st = h->stream;
-    const bool small = h->nl[0] < BLOCK3D_N;
     if (s == 0) {
-        if (!block3d<T>(st, L, L, F_HSS0, 1, false, 0, c, none, cst(R), none, rho, x, b1, ns))
-            STREAMCHK((pass3d<T, T>(st, L, F_HSS0, 1, false, 0, c, none, cst(R), none, rho, x, b1, ns)));
+        step3d<T>(st, L, F_HSS0, 1, false, 0, c, none, cst(R), none, rho, x, b1, ns);
     } else if (!block3d<T>(st, L, Bs, F_HSS, 1, false, 0, c, cst(u), cst(R), none, rho, x, b1, ns)) {
-        if (small) STREAMCHK(block3d<T>(st, Bs, Bs, F_RESID, 0, false, 0, c, cst(u), cst(R), none, nil, rho, nil, ns));
-        else STREAMCHK((pass3d<T, T>(st, Bs, F_RESID, 0, false, 0, c, cst(u), cst(R), none, nil, rho, nil, ns)));
+        step3d<T>(st, Bs, F_RESID, 0, false, 0, c, cst(u), cst(R), none, nil, rho, nil, ns);
         pre3d<T>(h, L, cst(rho), x, b1, ns);
     }
     for (int q = 0; q < h->cycles; ++q) {
         if (q > 0) {
             if (block3d<T>(st, L, L, F_JAC, 2, false, 0, (T)1, cst(x), cst(rho), none, nil, t, b1, ns)) {
                 std::swap(x, t);
-            } else if (small) {
-                STREAMCHK(block3d<T>(st, L, L, F_JAC, 1, false, 0, (T)1, cst(x), cst(rho), none, nil, t, nil, ns));
+            } else if (block3d<T>(st, L, L, F_JAC, 1, false, 0, (T)1, cst(x), cst(rho), none, nil, t, nil, ns)) {
                 STREAMCHK(block3d<T>(st, L, L, F_JAC, 1, false, 0, (T)1, cst(t), cst(rho), none, nil, x, b1, ns));
             } else {
-                STREAMCHK((pass3d<T, T>(st, L, F_JAC, 2, false, 0, (T)1, cst(x), cst(rho), none, nil, t, nil, ns)));
+                step3d<T>(st, L, F_JAC, 2, false, 0, (T)1, cst(x), cst(rho), none, nil, t, nil, ns);
                 std::swap(x, t);
-                STREAMCHK((pass3d<T, T>(st, L, F_JAC, 0, false, 0, (T)1, cst(x), cst(rho), none, nil, nil, b1, ns)));
+                step3d<T>(st, L, F_JAC, 0, false, 0, (T)1, cst(x), cst(rho), none, nil, nil, b1, ns);
             }
         }
         Vec<const cx<T>> ec = cst(vcycle3d_zero<T>(h, Lw, ws, 1, cst(b1), x1, t1, ns));

@@ -18,70 +18,14 @@
 // neighbourhood of (i, j): centre, east + west, north + south, diagonals.  A
 // boundary column has weights of its own, so the weights are per-lane values
 // and every column runs the same code.
+#pragma clang fp contract(off)
 #include <type_traits>
 
-#include "launch.h"
+#include "planes3d.h"
 
 namespace helm {
 
 namespace {
-
-template <typename T>
-__device__ __forceinline__ cx<T> csel(bool c, cx<T> a, cx<T> b) {
-    return mk(c ? a.x : b.x, c ? a.y : b.y);
-}
-
-// A plane as a buffer resource of the plane's size (0 outside the mesh): a
-// lane outside its range (offset OUTSIDE, or a plane of size 0) reads zero and
-// writes nothing.
-constexpr unsigned OUTSIDE = 0xFFFFFF00u;
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-template <typename V>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const cx<V>* base, int l, long long nodes, bool in) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<cx<V>*>(base + (long long)l * nodes), 0,
-                                             in ? (int)((unsigned)nodes * (unsigned)sizeof(cx<V>)) : 0, 0x00027000);
-}
-template <typename V>
-__device__ __forceinline__ cx<V> bload(__amdgpu_buffer_rsrc_t r, unsigned off) {
-    if constexpr (sizeof(V) == 8) {
-        return __builtin_bit_cast(cx<V>, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
-    } else {
-        return __builtin_bit_cast(cx<V>, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-    }
-}
-template <typename V>
-__device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, unsigned off, cx<V> v) {
-    if constexpr (sizeof(V) == 8) {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)off, 0, 0);
-    } else {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, 0);
-    }
-}
-
-// This column's weights: T = a a0 + h (east + west) + v (north + south) +
-// d (diagonals), d the same on every column.
-template <typename T>
-struct ColW {
-    cx<T> a, h, v, d;
-};
-template <typename T>
-__device__ __forceinline__ ColW<T> col_weights(const T (&r)[3], T k, const cx<T> (&e)[3], bool bx, bool by) {
-    const T fx = bx ? (T)1 : (T)0, fy = by ? (T)1 : (T)0;
-    ColW<T> w;
-    w.a = mk(r[0], (T)16 * k) + (fx + fy) * e[0] + (fx * fy) * e[2];
-    w.h = mk(r[1], (T)4 * k) + fy * e[1];
-    w.v = mk(r[1], (T)4 * k) + fx * e[1];
-    w.d = mk(r[2], k);
-    return w;
-}
-template <typename T>
-__device__ __forceinline__ cx<T> col_sum(const ColW<T>& w, cx<T> a0, cx<T> H, cx<T> V, cx<T> a2) {
-    return cfma(w.a, a0, cfma(w.h, H, cfma(w.v, V, w.d * a2)));
-}
-
-template <int U>
-using IC = std::integral_constant<int, U>;
 
 // FIRST, NJ, PRO, UPD, RR as for pass3d: the first stage, NJ Jacobi sweeps, P
 // e_c added to the input, Y += result, and the restriction of the last x's
@@ -149,9 +93,11 @@ __global__ __launch_bounds__(LW * LH) void k3_block(Op3F<T> L, Op3F<T> B, T s, V
     const int Z0 = seg * TZ, Z1 = min(Z0 + TZ, (RR ? nc : n) + 1);
     const int z0 = RR ? 2 * Z0 : Z0, z1 = RR ? min(2 * Z1, n + 1) : Z1;
     const int lb = (RR ? z0 - 1 : z0) - M;
-    auto rin = [&](const cx<T>* base, int l) { return plane_rsrc(base, l, sz, (unsigned)l <= (unsigned)n); };
-    auto rout = [&](cx<T>* base, int l) {
-        return plane_rsrc((const cx<T>*)base, l, sz, (unsigned)(l - z0) < (unsigned)(z1 - z0));
+    const unsigned szb = (unsigned)sz * (unsigned)sizeof(cx<T>);
+    auto plane = [&](const cx<T>* base, int l) { return reinterpret_cast<const char*>(base + (long long)l * sz); };
+    auto rin = [&](const cx<T>* base, int l) { return plane_rsrc(plane(base, l), szb, (unsigned)l <= (unsigned)n); };
+    auto rout = [&](const cx<T>* base, int l) {
+        return plane_rsrc(plane(base, l), szb, (unsigned)(l - z0) < (unsigned)(z1 - z0));
     };
     // this column's Jacobi factor on an interior plane and on an end plane
     auto od_of = [&](int q) { return csel(q < 2, csel(q == 0, L.od[0], L.od[1]), csel(q == 2, L.od[2], L.od[3])); };
@@ -242,14 +188,7 @@ __global__ __launch_bounds__(LW * LH) void k3_block(Op3F<T> L, Op3F<T> B, T s, V
             const cx<T> a2 = (c[-LW - 1] + c[-LW + 1]) + (c[LW - 1] + c[LW + 1]);
             const cx<T> t1 = col_sum(w1, a0, H, V, a2);
             cx<T> t0 = col_sum(w0, a0, H, V, a2);
-            if (pi == 0 || pi == n) {
-                // an end plane: T0 / 2 + cz times this column's mass pattern
-                const T fx = bx ? (T)1 : (T)0, fy = by ? (T)1 : (T)0;
-                const T ma = (T)16 - (T)8 * (fx + fy) + (T)4 * fx * fy, mh = (T)4 - (T)2 * fy, mv = (T)4 - (T)2 * fx;
-                const cx<T> m = mk(fmat(ma, a0.x, fmat(mh, H.x, fmat(mv, V.x, a2.x))),
-                                   fmat(ma, a0.y, fmat(mh, H.y, fmat(mv, V.y, a2.y))));
-                t0 = cfma(A.cz, m, (T)0.5 * t0);
-            }
+            if (pi == 0 || pi == n) t0 = end_term(A.cz, bx, by, a0, H, V, a2, t0);
             if (q >= 2) {
                 const int l = pi - 1;  // output plane
                 const cx<T> r = bv[k + q - 1] - (acc + t1);
@@ -292,14 +231,8 @@ __global__ __launch_bounds__(LW * LH) void k3_block(Op3F<T> L, Op3F<T> B, T s, V
             const int ci = q % RC, cj = q / RC % RCH, cl = q / (RC * RCH);
             const int I = RC * tx + ci, J = RCH * ty + cj, Lc = Z0 + cl;
             const cx<T>* c = r + 2 * cl * PLANE + (C::RIM + 2 * cj + 1) * LW + C::RIM + 2 * ci + 1;
-            cx<T> p[3];
-#pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                const cx<T>* d = c + u * PLANE;
-                p[u] = d[0] + (T)0.5 * ((d[-1] + d[1]) + (d[-LW] + d[LW])) +
-                       (T)0.25 * ((d[-LW - 1] + d[-LW + 1]) + (d[LW - 1] + d[LW + 1]));
-            }
-            cx<T> o = p[1] + (T)0.5 * (p[0] + p[2]);
+            cx<T> o = axpy_real((T)0.5, restrict_plane<T, LW>(c), restrict_plane<T, LW>(c + PLANE));
+            o = axpy_real((T)0.5, restrict_plane<T, LW>(c + 2 * PLANE), o);
             if (DIR && (((dm & 1u) && I == 0) || ((dm & 2u) && I == nc) || ((dm & 4u) && J == 0) ||
                         ((dm & 8u) && J == nc) || ((dm & 16u) && Lc == 0) || ((dm & 32u) && Lc == nc)))
                 o = z;
@@ -327,12 +260,20 @@ long long units_of(int n, int planes, int tz, int ns) {
 
 // A pass whose 16 x 16 regions of the smallest height fill the chip at most
 // twice runs with those; above that a wider region (less halo) if one a
-// compute unit suffices, else taller 16 x 16 ones up to the `most` workgroups
-// beyond which the marching passes win.  Measured (us per launch in FP64, 16 x
-// 16 / 32 x 16 / taller): prolongation + two sweeps 32^3 6.6 / 7.9 / 7.8, 48^3
-// 9.8 / 8.3 / 9.9, 64^3 19.7 / 24.0 / 19.0; pre-smoothing + restriction 32^3
-// 8.0 / 8.1 / 7.6, 48^3 11.7 / 8.5 / 9.7, 64^3 23.0 / 21.4 / 17.7.  The marching
-// passes took 15 and 13 us at 16^3 to 48^3, in two launches each.
+// compute unit suffices, else taller 16 x 16 ones.  Measured (us per launch in
+// FP64, 16 x 16 / 32 x 16 / taller): prolongation + two sweeps 32^3 6.6 / 7.9 /
+// 7.8, 48^3 9.8 / 8.3 / 9.9, 64^3 19.7 / 24.0 / 19.0; pre-smoothing +
+// restriction 32^3 8.0 / 8.1 / 7.6, 48^3 11.7 / 8.5 / 9.7, 64^3 23.0 / 21.4 /
+// 17.7.  The marching passes took 15 and 13 us at 16^3 to 48^3, in two launches
+// each.
+//
+// The halo costs nothing only while compute units would idle: from
+// BLOCK3D_BYTES a vector on, all columns counted, the marching passes win
+// whatever the mesh (kernels3d_columns.hip).  Measured (us per preconditioner of
+// four steps, blocks / marching): FP64 64^3 1 column (4.4 MB) 891 / 1087, 48^3 8
+// (15 MB) 1657 / 1246, 80^3 1 (8.5 MB) 1276 / 1190, 16 5591 / 4015 at 64^3 and
+// 10640 / 6176 at 80^3; FP32 64^3 2 (4.4 MB) 994 / 1122, 80^3 1 (4.3 MB) 956 /
+// 1038, 48^3 8 (7.5 MB) 1120 / 1045, 80^3 2 (8.5 MB) 1273 / 1250, 16 5733 / 3790.
 constexpr long long FEW = 512, ONE_EACH = 256;
 
 }  // namespace
@@ -350,6 +291,7 @@ bool block3d(hipStream_t st, const Op3F<T>& L, const Op3F<T>& B, int first, int 
         return true;                                                                                               \
     } while (0)
     if (n >= BLOCK3D_N) return false;
+    if ((long long)(n + 1) * (n + 1) * (n + 1) * ns * (long long)sizeof(cx<T>) > BLOCK3D_BYTES) return false;
     if (rr) {
         if (pro || upd != 0) return false;
         const int planes = n / 2 + 1;

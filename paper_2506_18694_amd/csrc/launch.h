@@ -228,13 +228,24 @@ bool pass3d(hipStream_t st, const Op3F<T>& L, int first, int nj, bool pro, int u
 // operator of F_HSS.  Supported: F_RESID, F_JAC with nj = 1, with nj = 2 and
 // pro (upd 0 or 1), and with the restriction F_JAC0 and F_HSS0 with nj = 1,
 // F_JAC with nj = 1 or 2 and F_HSS with nj = 1.  Returns false (and launches
-// nothing) for any other, for a level of BLOCK3D_N cells or more, and where
-// the three stages of the last two would not fit the chip at once.
+// nothing) for any other, for a level of BLOCK3D_N cells or more, for a launch
+// of more than BLOCK3D_BYTES a vector, and where the three stages of the last
+// two would not fit the chip at once.
 constexpr int BLOCK3D_N = 96;  // cells per side from which the marching passes are faster
+constexpr long long BLOCK3D_BYTES = 7000000;  // bytes of a vector (all columns) from which they are below that
 template <typename T>
 bool block3d(hipStream_t st, const Op3F<T>& L, const Op3F<T>& B, int first, int nj, bool pro, int upd, T s,
              Vec<const cx<T>> X, Vec<const cx<T>> Bv, Vec<const cx<T>> Ec, Vec<cx<T>> Rho, Vec<cx<T>> Y,
              Vec<cx<T>> Bc, int ns);
+
+// ---- the marching passes with the block passes' roundings (kernels3d_columns.hip)
+// For the launches below BLOCK3D_N that block3d declines; arguments as for
+// pass3d.  Supported: F_RESID, F_JAC with nj = 2, with or without pro (then upd
+// 0 or 1), and with the restriction F_JAC with nj = 0, F_HSS0 and F_JAC0 with
+// nj = 1.  Returns false (and launches nothing) for any other.
+template <typename T>
+bool columns3d(hipStream_t st, const Op3F<T>& L, int first, int nj, bool pro, int upd, T s, Vec<const cx<T>> X,
+               Vec<const cx<T>> Bv, Vec<const cx<T>> Ec, Vec<cx<T>> Rho, Vec<cx<T>> Y, Vec<cx<T>> Bc, int ns);
 
 // ---- mixed [DG0]^2 x P1 formulation (kernels2d_mixed.hip) ------------------
 // X, B, Y of mixed vectors [u | sigma] (sigma after the N = (n+1)^2 nodes).

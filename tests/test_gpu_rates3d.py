@@ -1,0 +1,36 @@
+"""Rates of the 3D passes against yardsticks measured beside them (the best of
+several timings each): many columns of a small mesh against fewer of a larger
+one with as many nodes."""
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+def _ms(f, reps):
+    f()
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(6):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(reps):
+            f()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1) / reps)
+    return best
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_columns_of_a_small_mesh_cost_what_their_nodes_do(precision):
+    from paper_2506_18694_amd import Solver
+    ms = {}
+    for n, levels, nrhs in ((80, 5, 16), (128, 6, 4)):  # 8.5M and 8.6M nodes
+        s = Solver(3, n, levels, n / 6.4, precision=precision, mg_cycles=3, hss_steps=4, restart=1)
+        v = torch.randn(nrhs, (n + 1) ** 3, dtype=torch.complex128, device="cuda")
+        ms[n] = _ms(lambda: s.precondition(v), 3)
+        s.close()
+    assert ms[80] < 1.25 * ms[128]
