@@ -202,6 +202,7 @@ struct Grid3F {
     int tiles_x, tiles_y, slots;     // tiles per side, columns
     int tz, segs, tz_e, segs_e;      // planes per segment and segments: interior and rim tiles
     unsigned eblocks;                // workgroups of the rim tiles
+    int split;                       // the rim's tiles are a list of their own (else all are "rim" tiles)
 };
 // first stage of a fused pass
 enum Pass3First : int {

@@ -112,24 +112,29 @@ __device__ __forceinline__ void plane_sums(const cx<T>* c, cx<T> (&a0)[R], cx<T>
     }
 }
 
-// Work unit of a workgroup: a tile and a segment of planes of one slot.  The
-// tiles on the mesh's rim come first: their columns on and outside the
-// boundary make a step dearer than an interior tile's, so
-// they take shorter segments (tz_e planes instead of tz), and are dealt over
-// all XCDs.  The others follow, each XCD taking a contiguous range, so that
-// neighbouring tiles of a segment share halo lines in one L2.  Returns false
-// for a spare workgroup.
+// Work unit of a workgroup: a tile and a segment of planes of one slot.  Where
+// the rim is split off (g.split) the tiles on the mesh's rim come first: their
+// columns on and outside the boundary make a step dearer than an interior
+// tile's, so they take shorter segments (tz_e planes instead of tz).  The others
+// follow.  Of either list each XCD takes a contiguous range, so that
+// neighbouring tiles of a segment share halo lines in one L2 (with the rim
+// tiles dealt over the XCDs in turn, which are most of the tiles up to 128^3, a
+// residual pass of four columns of 128^3 in FP32 took 56 us instead of 45).
+// Passes that memory bounds keep all tiles in one list: split, an XCD's tiles
+// are two strips with more halo between them and the other XCDs' (an
+// application at 256^3 in FP64 took 136 us).  Returns false for a spare
+// workgroup.
 struct Unit3 {
     int slot, tx, ty, z0, z1;
 };
 __host__ __device__ inline int rim_tiles(const Grid3F& g) {
-    return g.tiles_x > 2 && g.tiles_y > 2 ? 2 * g.tiles_x + 2 * (g.tiles_y - 2) : g.tiles_x * g.tiles_y;
+    return g.split && g.tiles_x > 2 && g.tiles_y > 2 ? 2 * g.tiles_x + 2 * (g.tiles_y - 2) : g.tiles_x * g.tiles_y;
 }
 __device__ __forceinline__ bool unit_of(const Grid3F& g, int planes, Unit3& u) {
     const unsigned E = (unsigned)rim_tiles(g), I = (unsigned)(g.tiles_x * g.tiles_y) - E;
     if (blockIdx.x < g.eblocks) {
         const unsigned per = E * (unsigned)g.segs_e;
-        unsigned b = blockIdx.x;
+        unsigned b = xcd_remap(blockIdx.x, g.eblocks);
         if (b >= per * (unsigned)g.slots) return false;
         u.slot = (int)(b / per);
         b %= per;
@@ -749,6 +754,7 @@ void launch_h(hipStream_t st, const Op3F<T>& L, T s, Vec<const cx<TI>> X, Vec<co
     g.tiles_x = (n + C::OWN) / C::OWN;
     g.tiles_y = (n + C::OWNH) / C::OWNH;
     g.slots = nslots;
+    g.split = C::M > 1 || RR || TH < LW;
     seg_planes(g, planes, RR ? 2 : 1, 3 * C::M + 2,
                resident_units<k3_march<T, TI, F, NJ, PRO, UPD, RR, DIR, TH, R, COLW>, THREADS>(),
                C::M > 1 || RR ? RIM_COST : RIM_COST_MEM);

@@ -1,5 +1,6 @@
 """Rates of the 3D passes against yardsticks measured beside them (the best of
-several timings each): many columns of a small mesh against fewer of a larger
+several timings each): a residual in FP32 against the FP64 one, which moves
+twice the bytes, and many columns of a small mesh against fewer of a larger
 one with as many nodes."""
 
 import pytest
@@ -22,6 +23,24 @@ def _ms(f, reps):
         torch.cuda.synchronize()
         best = min(best, e0.elapsed_time(e1) / reps)
     return best
+
+
+def _step(n, levels, nrhs, precision):
+    from paper_2506_18694_amd import Solver
+    dt = torch.complex128 if precision == "fp64" else torch.complex64
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x, b, y = (torch.randn(nrhs, (n + 1) ** 3, dtype=dt, device="cuda", generator=g) for _ in range(3))
+    s = Solver(3, n, levels, n / 6.4, precision=precision, mg_cycles=2, hss_steps=1, restart=1)
+    return s, x, b, y
+
+
+def test_fp32_residual_of_several_columns_takes_half_of_the_fp64_one():
+    ms = {}
+    for precision in ("fp64", "fp32"):  # half the bytes
+        s, x, b, y = _step(128, 5, 4, precision)
+        ms[precision] = _ms(lambda: s.hss_residual(b, x), 40)
+        s.close()
+    assert ms["fp32"] < 0.5 * ms["fp64"]
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
