@@ -8,10 +8,24 @@ namespace helm {
 
 namespace {
 
+// Two columns a thread on 32 x 32 regions, but one for the FP32 residual, whose
+// instructions are then fewer than what the barrier per plane costs: on 32 x 16
+// regions up to 4M nodes, whose launches are short of workgroups, above that on
+// 32 x 32.  Measured (us, two columns / 32 x 16 / 32 x 32): 96^3 9.9 / 9.1 / 9.7,
+// 128^3 12.7 / 12.7 / 13.4, 4 x 128^3 42.0 / 47.6 / 40.5, 256^3 99.3 / 103.8 /
+// 93.9.  The other one-stage passes gain nothing from one column a thread: an
+// application at 256^3 in FP64 113.5 / 142.8 / 115.9, at 128^3 16.3 / 16.5 / 16.5.
+constexpr double RESID_TALL = 4e6;
 template <typename T, typename TI, int F, int NJ, bool PRO, int UPD, bool RR>
 void launch_pass(hipStream_t st, const Op3F<T>& L, T s, Vec<const cx<TI>> X, Vec<const cx<T>> Bv,
                  Vec<const cx<T>> Ec, Vec<cx<T>> Rho, Vec<cx<T>> Y, Vec<cx<T>> Bc, int nslots) {
-    launch_d<T, TI, F, NJ, PRO, UPD, RR, 32, 2>(st, L, s, X, Bv, Ec, Rho, Y, Bc, nslots);
+    if constexpr (sizeof(T) == 4 && F == F_RESID) {
+        const double nodes = (double)(L.n + 1) * (L.n + 1) * (L.n + 1) * nslots;
+        if (nodes < RESID_TALL) launch_d<T, TI, F, NJ, PRO, UPD, RR, 16, 1>(st, L, s, X, Bv, Ec, Rho, Y, Bc, nslots);
+        else launch_d<T, TI, F, NJ, PRO, UPD, RR, 32, 1>(st, L, s, X, Bv, Ec, Rho, Y, Bc, nslots);
+    } else {
+        launch_d<T, TI, F, NJ, PRO, UPD, RR, 32, 2>(st, L, s, X, Bv, Ec, Rho, Y, Bc, nslots);
+    }
 }
 
 }  // namespace

@@ -220,7 +220,9 @@ struct March {
     static constexpr int PF = 2;  // input planes requested ahead of the one in LDS
     // ring of the right-hand side: PF ahead of its first use, kept to its last
     static constexpr int BR = PF + 2 * (M - 1) + (J0 ? 2 : 0);
-    static constexpr int UNR = BR < 4 ? 4 : BR;
+    // (two steps where there is one stage: a launch of a few planes a workgroup
+    // runs every copy of a step once, and their code has to be fetched)
+    static constexpr int UNR = M == 1 && !RR ? 2 : BR < 4 ? 4 : BR;
     static_assert(M == 1 || M == 2, "one or two stages");
     static_assert(UNR % PF == 0 && UNR % 2 == 0 && UNR % BR == 0, "unroll must cover the rings");
     static_assert(!(PRO && (FIRST != F_JAC || RR)), "the prolongation feeds plain sweeps");
@@ -295,7 +297,7 @@ __global__ __launch_bounds__(LW * TH / R) void k3_march(Op3F<T> L, T s, Vec<cons
     // the last stage's output planes [qf, ql], and the steps that give them
     const int qf = RR ? z0 - 1 : z0, ql = RR ? 2 * Z1 - 1 : z1 - 1;
     int p0 = qf - M;
-    p0 -= p0 & 1;  // an even first plane
+    if (PRO || RR) p0 -= p0 & 1;  // an even first plane: the coarse planes follow the step's parity
     const int p1 = ql + 2 * M - 1 + (RR ? 1 : 0);
     const int hi = min(ql + M, n);  // last input plane needed
     // planes l of an input (outside the mesh, or past the last one needed: none)

@@ -1,5 +1,6 @@
 """Rates of the 3D passes against yardsticks measured beside them (the best of
-several timings each): a residual in FP32 against the FP64 one, which moves
+several timings each): an operator pass against a copy of the vector, which
+moves the same bytes, a residual in FP32 against the FP64 one, which moves
 twice the bytes, and many columns of a small mesh against fewer of a larger
 one with as many nodes."""
 
@@ -32,6 +33,12 @@ def _step(n, levels, nrhs, precision):
     x, b, y = (torch.randn(nrhs, (n + 1) ** 3, dtype=dt, device="cuda", generator=g) for _ in range(3))
     s = Solver(3, n, levels, n / 6.4, precision=precision, mg_cycles=2, hss_steps=1, restart=1)
     return s, x, b, y
+
+
+def test_operator_runs_near_the_copy_rate():
+    s, x, b, y = _step(256, 6, 1, "fp64")
+    assert _ms(lambda: s.apply("L", x), 20) < 1.2 * _ms(lambda: y.copy_(x), 20)
+    s.close()
 
 
 def test_fp32_residual_of_several_columns_takes_half_of_the_fp64_one():
