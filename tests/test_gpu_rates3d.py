@@ -1,8 +1,7 @@
 """Rates of the 3D passes against yardsticks measured beside them (the best of
 several timings each): an operator pass against a copy of the vector, which
-moves the same bytes, a residual in FP32 against the FP64 one, which moves
-twice the bytes, and many columns of a small mesh against fewer of a larger
-one with as many nodes."""
+moves the same bytes, a residual against an addition of its vectors, and many
+columns of a small mesh against fewer of a larger one with as many nodes."""
 
 import pytest
 
@@ -41,13 +40,11 @@ def test_operator_runs_near_the_copy_rate():
     s.close()
 
 
-def test_fp32_residual_of_several_columns_takes_half_of_the_fp64_one():
-    ms = {}
-    for precision in ("fp64", "fp32"):  # half the bytes
-        s, x, b, y = _step(128, 5, 4, precision)
-        ms[precision] = _ms(lambda: s.hss_residual(b, x), 40)
-        s.close()
-    assert ms["fp32"] < 0.5 * ms["fp64"]
+def test_residual_of_many_columns_runs_near_the_rate_of_an_addition():
+    # 16 columns of 128^3: 275 MB a vector, beyond every cache
+    s, x, b, y = _step(128, 6, 16, "fp32")
+    assert _ms(lambda: s.hss_residual(b, x), 20) < 1.7 * _ms(lambda: torch.add(b, x, out=y), 20)
+    s.close()
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
