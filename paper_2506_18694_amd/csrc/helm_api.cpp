@@ -456,7 +456,13 @@ void op3d(helm_t* h, hipStream_t st, const Coef& cf, int l, int mode, T s, Vec<c
           Vec<const cx<T>> B, Vec<cx<T>> Y, int ns) {
     const int first = mode == MODE_APPLY ? F_APPLY : mode == MODE_RESID ? F_RESID : F_JAC;
     bool fused = fused3d(h) && (mode == MODE_APPLY || mode == MODE_RESID);
-    if constexpr (std::is_same<T, TI>::value) fused = fused || (fused3d(h) && mode == MODE_JACOBI);
+    if constexpr (std::is_same<T, TI>::value) {
+        fused = fused || (fused3d(h) && mode == MODE_JACOBI);
+        if (fused3d(h) && mode == MODE_JACOBI0) {
+            jacobi0_3d<T>(st, make_op3f<T>(cf, h->nl[l], h->omega), B, Y, ns);
+            return;
+        }
+    }
     if (fused) {
         STREAMCHK((pass3d<T, TI>(st, make_op3f<T>(cf, h->nl[l], h->omega, h->dir), first,
                                  mode == MODE_JACOBI ? 1 : 0, false, 0, s, X, B, Vec<const cx<T>>{}, Vec<cx<T>>{}, Y,

@@ -224,6 +224,10 @@ template <typename T, typename TI>
 bool pass3d(hipStream_t st, const Op3F<T>& L, int first, int nj, bool pro, int upd, T s, Vec<const cx<TI>> X,
             Vec<const cx<T>> Bv, Vec<const cx<T>> Ec, Vec<cx<T>> Rho, Vec<cx<T>> Y, Vec<cx<T>> Bc, int nslots);
 
+// y = w/D b on any level: the sweep from a zero guess alone.
+template <typename T>
+void jacobi0_3d(hipStream_t st, const Op3F<T>& L, Vec<const cx<T>> B, Vec<cx<T>> Y, int ns);
+
 // ---- the same stages on small 3D levels (kernels3d_block.hip) --------------
 // One pass on whole blocks of the mesh; arguments as for pass3d, B the second
 // operator of F_HSS.  Supported: F_RESID, F_JAC with nj = 1, with nj = 2 and

@@ -1,7 +1,8 @@
 """Rates of the 3D passes against yardsticks measured beside them (the best of
-several timings each): an operator pass against a copy of the vector, which
-moves the same bytes, a residual against an addition of its vectors, and many
-columns of a small mesh against fewer of a larger one with as many nodes."""
+several timings each): an operator pass and the zero-guess sweep against a copy
+of the vector, which moves the same bytes, a residual against an addition of its
+vectors, and many columns of a small mesh against fewer of a larger one with as
+many nodes."""
 
 import pytest
 
@@ -44,6 +45,12 @@ def test_residual_of_many_columns_runs_near_the_rate_of_an_addition():
     # 16 columns of 128^3: 275 MB a vector, beyond every cache
     s, x, b, y = _step(128, 6, 16, "fp32")
     assert _ms(lambda: s.hss_residual(b, x), 20) < 1.7 * _ms(lambda: torch.add(b, x, out=y), 20)
+    s.close()
+
+
+def test_zero_guess_sweep_runs_near_the_copy_rate():
+    s, x, b, y = _step(128, 6, 16, "fp32")
+    assert _ms(lambda: s.jacobi(b), 20) < 1.2 * _ms(lambda: y.copy_(x), 20)
     s.close()
 
 
