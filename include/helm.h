@@ -144,10 +144,15 @@ typedef struct {
     int    x0_given;   /* 1: x holds the initial guess on entry, else x0 = 0 */
     int    profile;    /* 1: time the finest-level smoothing launches of
                           every tenth HSS step with HIP events (2D: the
-                          four-sweep passes; 3D: each Jacobi sweep; fills
-                          the sweep_* stats).  A timed solve runs its
-                          preconditioner eagerly, without the captured
-                          graphs                                            */
+                          four-sweep passes; 3D: the prolongation with both
+                          post-smoothing sweeps; fills the sweep_* stats).  A
+                          timed solve runs its preconditioner eagerly,
+                          without the captured graphs, and its timed 2D
+                          launches hold the finest level alone: on small
+                          meshes, where an untimed step shares that launch
+                          with the next coarser level, they are not the
+                          launches of an untimed solve (the results are the
+                          same, bit for bit)                                */
     int    mg_cycles;  /* V-cycles per inner HSS solve (each after the first
                           starts from the previous iterate).  0 = automatic:
                           with exact inner solves the HSS error contracts by
@@ -166,8 +171,9 @@ typedef struct {
                           private stream, launched on the handle's stream)  */
     int    no_small;   /* 1: run every 2D level with per-level kernels; by
                           default the levels from the first one whose
-                          vectors fit one workgroup's LDS down to the
-                          coarsest run as one LDS-resident kernel per cycle  */
+                          vectors fit one workgroup's LDS down to a coarsest
+                          mesh of at most 100 nodes run as one LDS-resident
+                          kernel per cycle                                   */
     int    verbose;    /* > 0: print the Arnoldi residual estimate to stderr
                           every `verbose` outer iterations                   */
     int    no_stream;  /* 1: run the large 2D levels with the LDS-tiled
@@ -176,8 +182,10 @@ typedef struct {
                           the register-streaming kernels (one wavefront
                           marches up a strip of 64 columns, every sweep a
                           pipeline stage one row behind the previous one)
-                          and the 3D levels >= 128^3 with the z-marching
-                          column-tile kernel                                 */
+                          or, where a launch is small, the same passes on
+                          LDS tiles, and the 3D levels with z-marching
+                          passes or, where a launch is small, passes on
+                          whole blocks of the mesh                           */
     int    full_reorth; /* 1: classical Gram-Schmidt twice at every Arnoldi
                           step; by default the second pass runs only for
                           the columns whose first pass kept less than
@@ -223,7 +231,7 @@ typedef struct {
                                     right-hand side: x and b read, x' written;
                                     2D adds the coarse correction read and the
                                     coarse residual written (a quarter vector
-                                    each)                                      */
+                                    each), 3D the coarse correction (an eighth) */
     int    mg_cycles;            /* V-cycles per inner HSS solve used          */
     double vcycle_rate;          /* measured V-cycle contraction (automatic
                                     mode; 0 when mg_cycles was given)         */

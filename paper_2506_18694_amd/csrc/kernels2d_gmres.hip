@@ -18,11 +18,11 @@
 // one chunk each a smoothing took 3.20 ms at 2048^2 and 38.3 at 4096^2, where
 // 56 launches took 1.60 and 6.76; now 1.11 and 5.14 (with at most 256 workgroups
 // 1.28 and 7.45, with 512 1.11 and 4.97, with 1024 1.14 and 5.16).  The count
-// follows from the nodes alone: a
-// column's sums do not depend on how many columns share the launch.  Both
-// keep the Krylov vectors unnormalised, w_0 = r and w_{j+1} the vector before
-// its division by h_{j+1,j}, with their norms beside them: V_i = w_i / |w_i|
-// enters through its scale, and no pass normalises.
+// follows from the nodes alone: a column's sums do not depend on how many
+// columns share the launch.  Both forms keep the Krylov vectors unnormalised,
+// w_0 = r and w_{j+1} the vector before its division by h_{j+1,j}, with their
+// norms beside them: V_i = w_i / |w_i| enters through its scale, and no pass
+// normalises.
 // Measured per smoothing (m = 5, one column): about 190 us as 56 launches; 19 us
 // in one workgroup at 576 nodes, 33 at 2209, and 75 us as 17 launches at 8649
 // to 34225, 115 at 512^2 (270 as 56).  The one-workgroup form is a chain of 16

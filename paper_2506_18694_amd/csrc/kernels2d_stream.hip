@@ -437,7 +437,7 @@ __global__ __launch_bounds__(WAVE * SW) __attribute__((amdgpu_waves_per_eu(2))) 
         if (PROLONG) x0 = axpy_real((T)0.5, in.e0 + in.e1, x0);
         ring_push<P>(rg[0], dclip<DIR>(clip<MODE>(x0, ln, t, n), L, ln, t));
         bq[P % NB] = in.b;
-// a call per sweep: as an unrolled loop the kernels spill more scalar
+        // a call per sweep: as an unrolled loop the kernels spill more scalar
         // registers (FP32 four sweeps 43 instead of 19)
         auto sweep = [&](auto sc) {
             constexpr int s = decltype(sc)::value;

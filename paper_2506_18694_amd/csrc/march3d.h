@@ -35,17 +35,20 @@
 // restriction of the residual (in-plane weights 1, 1/2, 1/4; across planes 1/2,
 // 1, 1/2).
 //
-// What bounds it: in FP64 at 256^3 a two-sweep pass moves 0.98 GB (815 MB
-// without the halo) in 205 us, 4.8 TB/s where a device copy reaches 5.1; its 8
-// wavefronts per CU (211 to 237 VGPRs) are active half of the time and wait for
-// LDS and barriers a third of it.  In FP32 the instructions bound it.  Two
-// sweeps a pass take 205 us instead of 330 in two passes, with the prolongation
-// 215 instead of 327, the residual restriction 135 (144 before), both
-// zero-guess sweeps with it 207 (305); in FP32 137 (157 before), 147 (169), 70
-// (85) and 148 us.  Three stages a pass spill (508 us for two sweeps and the
-// restriction, against 340 in two passes), one column a thread on 1024 threads
-// has no registers left (242 us), and 24-row regions double the rim in FP32
-// (155 us).
+// What bounds it: in FP64 at 256^3 the prolongation with two sweeps moves 0.97
+// GB (849 MB without the halo) in 196 us, 4.9 TB/s where a device copy reaches
+// 5.1; the two-stage passes keep 8 wavefronts per CU (209 to 235 VGPRs), active
+// half of the time and waiting for LDS and barriers a third of it.  The update
+// pass (UPD) takes all 256 VGPRs and spills 12 (24 with Dirichlet faces): 250 us,
+// 220 for its bytes.  In FP32 the instructions bound them.  Median times in a
+// solve at 256^3, FP64 and FP32, with the passes of one stage (FP64) and of 512
+// threads (FP32) that they replaced: two sweeps 188 us (330 in two) and 115
+// (157), with the prolongation 196 (327) and 127 (169), the residual restriction
+// 140 (144) and 68 (85), both zero-guess sweeps with it 188 (305) and 136; the
+// HSS residual 156 (176) and 82.  Three stages a pass spill (508 us for two
+// sweeps and the restriction, against 340 in two passes), one column a thread
+// on 1024 threads has no registers left (242 us), and 24-row regions double the
+// rim in FP32 (155 us).
 #pragma once
 
 #include <algorithm>

@@ -1,11 +1,14 @@
 // Device helpers of the two kinds of fused 3D pass (kernels3d_fused.hip,
 // kernels3d_block.hip): planes read and written through buffer resources, and
-// the terms of a node's row.  Both kinds use the same formulas term by term,
+// the terms of a node's row, by the weights of the interior and the boundary's
+// terms (the marching passes) or by weights of the column (the block passes, and
+// the marching passes that take their place for many columns,
+// kernels3d_columns.hip).  Passes of one kind use the same formulas term by term,
 // and nothing lets the compiler fuse a product into a sum (the files that
 // include this switch contraction off before any include), so that a node's
-// value does not depend on the kind or form of the pass that computes it: the
-// size of a launch alone decides which runs, and a column's result does not
-// depend on how many columns share it.
+// value does not depend on the form of the pass that computes it: the kind
+// follows from the mesh, the form from the size of the launch, and a column's
+// result does not depend on how many columns share it.
 #pragma once
 
 #include <type_traits>
