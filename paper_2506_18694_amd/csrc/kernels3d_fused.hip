@@ -28,12 +28,15 @@ void launch_pass(hipStream_t st, const Op3F<T>& L, T s, Vec<const cx<TI>> X, Vec
     }
 }
 
-// y = w/D b, the sweep from a zero guess: four nodes a thread, gx workgroups a
+// y = w/D b, the sweep from a zero guess: 16 bytes a thread, gx workgroups a
 // plane of the mesh.  The factors come from the table of the number of boundary
 // coordinates and a node's place from one 32-bit division: with the division of
-// the diagonal and 64-bit ones at every node it took 141 us instead of 95 (a
-// copy: 99) on 16 columns of 128^3 in FP32.
-constexpr int J0_BS = 256, J0_NPT = 4;
+// the diagonal and 64-bit ones at every node it took 59 us on 256^3 in FP32,
+// now 43.  Nodes a thread, 1 / 2 / 4: FP32 53 / 43 / 43 us, two columns 118 / 94
+// / 99; FP64 91 / 96 / 101, where the instructions never counted.
+constexpr int J0_BS = 256;
+template <typename T>
+constexpr int J0_NPT = 16 / (int)sizeof(cx<T>);
 template <typename T>
 __global__ __launch_bounds__(J0_BS) void k3_jacobi0(Op3F<T> L, Vec<const cx<T>> Bv, Vec<cx<T>> Y, unsigned gx) {
     const unsigned n = (unsigned)L.n, sy = n + 1, sz = sy * sy;
@@ -42,15 +45,16 @@ __global__ __launch_bounds__(J0_BS) void k3_jacobi0(Op3F<T> L, Vec<const cx<T>> 
     const long long base = (long long)l * sz;
     const cx<T>* b = Bv.at((int)slot) + base;
     cx<T>* y = Y.at((int)slot) + base;
-    cx<T> v[J0_NPT];
+    constexpr int NPT = J0_NPT<T>;
+    cx<T> v[NPT];
 #pragma unroll
-    for (int u = 0; u < J0_NPT; ++u) {
-        const unsigned t = (blk * J0_NPT + u) * J0_BS + threadIdx.x;
+    for (int u = 0; u < NPT; ++u) {
+        const unsigned t = (blk * NPT + u) * J0_BS + threadIdx.x;
         v[u] = b[t < sz ? t : 0];
     }
 #pragma unroll
-    for (int u = 0; u < J0_NPT; ++u) {
-        const unsigned t = (blk * J0_NPT + u) * J0_BS + threadIdx.x;
+    for (int u = 0; u < NPT; ++u) {
+        const unsigned t = (blk * NPT + u) * J0_BS + threadIdx.x;
         if (t >= sz) continue;
         const unsigned j = t / sy, i = t - j * sy;
         const int q = (int)(i == 0 || i == n) + (int)(j == 0 || j == n) + (int)(l == 0 || l == n);
@@ -93,7 +97,7 @@ bool pass3d(hipStream_t st, const Op3F<T>& L, int first, int nj, bool pro, int u
 
 template <typename T>
 void jacobi0_3d(hipStream_t st, const Op3F<T>& L, Vec<const cx<T>> B, Vec<cx<T>> Y, int ns) {
-    const unsigned sz = (unsigned)(L.n + 1) * (unsigned)(L.n + 1), per = J0_BS * J0_NPT;
+    const unsigned sz = (unsigned)(L.n + 1) * (unsigned)(L.n + 1), per = J0_BS * J0_NPT<T>;
     const unsigned gx = (sz + per - 1) / per;
     k3_jacobi0<T><<<gx * ((unsigned)L.n + 1) * (unsigned)ns, J0_BS, 0, st>>>(L, B, Y, gx);
 }
