@@ -64,7 +64,7 @@ DOMINANT = {
     2: {"tag": "k_stream_sweeps4", "sources": ("kernels2d_stream.hip", "helm_common.h", "stencil_rows.h"),
         "desc": "finest-level prolongation + four Jacobi sweeps + residual restriction "
                 "(k_stream_sweeps<S=4>); x, b, e_c read, x', b_c written"},
-    3: {"tag": "k3_march_prolong", "sources": ("march3d.h", "planes3d.h", "kernels3d_fused.hip", "helm_common.h"),
+    3: {"tag": "k3_march_prolong", "sources": ("march3d.h", "planes3d.h", "helm_common.h"),
         "desc": "finest-level prolongation + two Jacobi sweeps in one z-marching pass "
                 "(k3_march<F_JAC, 2 sweeps, prolong>); x, b, e_c read, x' written: 3.125 S N"},
 }
