@@ -117,9 +117,9 @@ template <typename T>
 __device__ __forceinline__ ColW<T> col_weights(const T (&r)[3], T k, const cx<T> (&e)[3], bool bx, bool by) {
     const T fx = bx ? (T)1 : (T)0, fy = by ? (T)1 : (T)0;
     ColW<T> w;
-    w.a = mk(r[0], (T)16 * k) + (fx + fy) * e[0] + (fx * fy) * e[2];
-    w.h = mk(r[1], (T)4 * k) + fy * e[1];
-    w.v = mk(r[1], (T)4 * k) + fx * e[1];
+    w.a = axpy_real(fx * fy, e[2], axpy_real(fx + fy, e[0], mk(r[0], (T)16 * k)));
+    w.h = axpy_real(fy, e[1], mk(r[1], (T)4 * k));
+    w.v = axpy_real(fx, e[1], mk(r[1], (T)4 * k));
     w.d = mk(r[2], k);
     return w;
 }
